@@ -42,16 +42,14 @@ int default_zs(int tiles_xy, int nz, int target_groups)
     return (nz + best - 1) / best;
 }
 
-int resident_groups(const void* kernel, int threads)
+int device_cus()
 {
     constexpr int kMaxDev = 64;
     static std::atomic<int> cus[kMaxDev];  // CU count per device, 0 = not queried yet
-    static std::mutex mu;
-    static std::map<std::pair<const void*, int>, int> per_cu;  // resident groups per CU
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) {
         (void)hipGetLastError();
-        return 1024;
+        return 256;
     }
     int n = cus[dev].load(std::memory_order_relaxed);
     if (n <= 0) {
@@ -62,6 +60,13 @@ int resident_groups(const void* kernel, int threads)
         }
         cus[dev].store(n, std::memory_order_relaxed);
     }
+    return n;
+}
+
+int resident_groups(const void* kernel, int threads)
+{
+    static std::mutex mu;
+    static std::map<std::pair<const void*, int>, int> per_cu;  // resident groups per CU
     int k = 0;
     {
         std::lock_guard<std::mutex> lk(mu);
@@ -77,7 +82,7 @@ int resident_groups(const void* kernel, int threads)
             per_cu[{kernel, threads}] = k;
         }
     }
-    return n * k;
+    return device_cus() * k;
 }
 
 int check_volume_args(const lnf_ctx* h, const void* vol, const int64_t dims[3], int dtype,

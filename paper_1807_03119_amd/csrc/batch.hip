@@ -45,16 +45,16 @@ constexpr int kSlots = 4;         // job-table staging slots of eager calls, use
 constexpr int kCaptureSlots = 4;  // slots of calls captured in a graph, one per capture
 
 template <int R, int TY, typename T, bool GATE, int TXW, bool QUEUE>
-__global__ __launch_bounds__((M9Geo<R, TY, TXW>::THREADS))
-__attribute__((amdgpu_waves_per_eu((m9_waves<R, M9Geo<R, TY, TXW>::THREADS>())))) void mean9_multi(
+__global__ __launch_bounds__((M9Geo<R, TY, TXW, T>::THREADS))
+__attribute__((amdgpu_waves_per_eu((m9_waves<R, TY, T>())))) void mean9_multi(
     BatchTable* __restrict__ tab, int cls, uint32_t gate)
 {
-    __shared__ __align__(16) M9SmemAny<R, TY, TXW, T> sm;
+    __shared__ __align__(16) M9Smem<R, TY, TXW, T> sm;
     __shared__ int s_t;
     constexpr int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
     for_class_tiles<TXW, TY, QUEUE>(tab, cls, &s_t, [&](const BatchJobDesc& d, int x0, int y0,
                                                        int z0, int z1, int tid) {
-        mean9_tile<R, TY, T, GATE, TXW>(sm, d.pairs != 0, static_cast<const T*>(d.in),
+        mean9_tile<R, TY, T, GATE, TXW>(sm, d.words != 0, static_cast<const T*>(d.in),
                                         static_cast<T*>(d.out), Geom{d.nx, d.ny, d.nz}, x0, y0,
                                         z0, z1, gate, 1.0 / (9.0 * n), tid);
     });
@@ -81,7 +81,7 @@ template <int R, typename T, bool GATE, int TY, int TXW, bool QUEUE>
 ClassKernel mean9_kernel()
 {
     return {reinterpret_cast<const void*>(mean9_multi<R, TY, T, GATE, TXW, QUEUE>),
-            M9Geo<R, TY, TXW>::THREADS};
+            M9Geo<R, TY, TXW, T>::THREADS};
 }
 
 // Queue mode is compiled for the 64 x 16 tile only.
@@ -90,9 +90,9 @@ ClassKernel mean9_kernel_v(int variant, bool queue)
 {
     if (queue) return mean9_kernel<R, T, GATE, 16, 64, true>();
     switch (variant) {
-    case 1: return mean9_kernel<R, T, GATE, 32, 64, false>();
+    case 1: return mean9_kernel<R, T, GATE, 32, 128, false>();
     case 2: return mean9_kernel<R, T, GATE, 16, 32, false>();
-    case 3: return mean9_kernel<R, T, GATE, 32, 32, false>();
+    case 3: return mean9_kernel<R, T, GATE, 16, 128, false>();
     default: return mean9_kernel<R, T, GATE, 16, 64, false>();  // variant 0: 64 x 16
     }
 }
@@ -295,8 +295,16 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
     BatchSlot& s = *sp;
 
     // order: by class, then larger jobs first (their tiles get the low indices)
-    std::vector<int> order(n);
-    for (int i = 0; i < n; ++i) order[i] = i;
+    std::vector<int> order;
+    for (int i = 0; i < n; ++i) {
+        if (h->rule != LNF_MEAN9 || h->geom || mean9_plane_ok(jobs[i].dtype, geoms[i])) {
+            order.push_back(i);
+        } else if (launch_rule(h->rule, h->geom, jobs[i].in, jobs[i].out, jobs[i].dtype, jobs[i].radius,
+                               geoms[i], h->gate, TileCfg{-1, 0}, stream) != hipSuccess) {
+            return LNF_EHIP;
+        }
+    }
+    n = (int)order.size();
     auto vox = [&](int i) { return (double)geoms[i].nx * geoms[i].ny * geoms[i].nz; };
     std::sort(order.begin(), order.end(), [&](int a, int b) {
         const int ca = batch_class(jobs[a].radius, jobs[a].dtype);
@@ -320,7 +328,7 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
         const int r = c / 2 + 1, dtype = (c & 1) ? LNF_U16 : LNF_U8;
         // tile variant: the tuned one of the class's largest volume, else the
         // default for that volume
-        int variant = 0, tx = 32, ty = 8;
+        int variant = 0, tx = 32, ty = 8, depth = 0;
         const TileCfg cfg = ctx_tile(h, h->rule, dtype, r, geoms[order[k]]);
         if (h->geom) {
             gk[c] = geometry_class_kernel(h->rule, h->geom, dtype, r);
@@ -329,10 +337,11 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
             ty = gk[c].ty;
         } else {
             if (h->rule == LNF_MEAN9) {
-                variant = queue ? 0
-                          : cfg.variant >= 0 && cfg.variant < mean9_variants()
-                              ? cfg.variant
-                              : mean9_default_variant(dtype, r);
+                std::vector<Geom> members;
+                for (int q = k; q < kend; ++q) members.push_back(geoms[order[q]]);
+                const TileCfg m = mean9_class_tile(queue ? 0 : cfg.variant, dtype, r, members);
+                variant = m.variant;
+                depth = m.zs;
                 mean9_tile_shape(variant, &tx, &ty);
             } else {
                 variant = cfg.variant >= 0 && cfg.variant < minvar9_variants()
@@ -346,7 +355,8 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
         // differ in length and the launch ends on a tail of the longest ones.
         // About 16 workgroups per resident slot keep that tail short (measured
         // on 64 mixed volumes: 1.38 ms against 1.61 ms for one strip per
-        // column); strips stay at least 16 slices deep
+        // column); strips stay at least 16 slices deep.  MEAN9 classes take the
+        // depth of least estimated time instead (mean9_class_tile).
         const long long target = resident_groups(kern[c].fn, kern[c].threads);
         long long cols = 0;
         for (int q = k; q < kend; ++q) {
@@ -363,8 +373,8 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
             d.nx = g.nx;
             d.ny = g.ny;
             d.nz = g.nz;
-            d.pairs = mean9_pairs_ok(d.in, g.nx, dtype == LNF_U8 ? 1 : 2) ? 1 : 0;
-            const int nzs = std::min(nzs_want, std::max(1, g.nz / 16));
+            d.words = mean9_words_ok(d.in, d.out, g.nx) ? 1 : 0;
+            const int nzs = depth > 0 ? (g.nz + depth - 1) / depth : std::min(nzs_want, std::max(1, g.nz / 16));
             d.zs = (g.nz + nzs - 1) / nzs;
             d.tiles_x = (g.nx + tx - 1) / tx;
             d.tiles_y = (g.ny + ty - 1) / ty;

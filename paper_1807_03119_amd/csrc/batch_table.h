@@ -19,7 +19,7 @@ struct BatchJobDesc {
     void* out;
     int nx, ny, nz;
     int tiles_x, tiles_y, zs, tile_begin;  // tile_begin: first tile in its class
-    int pairs;                             // MEAN9 stages element pairs (mean9_pairs_ok)
+    int words;                             // MEAN9 stores 32-bit words (mean9_words_ok)
 };
 
 // Queue mode keeps each XCD's counter in a 128-byte line of its own: device-scope

@@ -66,19 +66,13 @@ __device__ __forceinline__ uint32_t buffer_load<uint16_t>(rsrc_t r, uint32_t vof
 // per launch (FETCH_SIZE) fell from 432 to 357 MB and the rate rose by 10-15 %.
 constexpr int kStoreNT = 2;
 
-template <typename T>
-__device__ __forceinline__ void buffer_store(uint32_t v, rsrc_t r, uint32_t voff, uint32_t soff);
-template <>
-__device__ __forceinline__ void buffer_store<uint8_t>(uint32_t v, rsrc_t r, uint32_t voff,
-                                                      uint32_t soff)
+template <typename T, int POLICY = kStoreNT>
+__device__ __forceinline__ void buffer_store(uint32_t v, rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)v, r, voff, soff, kStoreNT);
-}
-template <>
-__device__ __forceinline__ void buffer_store<uint16_t>(uint32_t v, rsrc_t r, uint32_t voff,
-                                                       uint32_t soff)
-{
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, voff, soff, kStoreNT);
+    if constexpr (sizeof(T) == 1)
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)v, r, voff, soff, POLICY);
+    else
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, voff, soff, POLICY);
 }
 
 // Direct buffer -> LDS load of one element per lane (LDS DMA).  The element is

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 #include "lnf.h"
 
@@ -25,18 +26,29 @@ struct TileCfg {
 
 // ---- MEAN9 (mean of the nine cluster means) -------------------------------
 int mean9_variants();
-int mean9_default_variant(int dtype, int r);
+// Tile variant and z-strip depth for one launch over many volumes (the class
+// of a batch); variant < 0: the best one, else that one's depth.
+TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>& g);
 // Tile footprint of a variant: output tile width/height in x/y.
 void mean9_tile_shape(int variant, int* tx, int* ty);
 // With plan != nullptr the launchers only resolve the configuration they
 // would launch (tile variant and z-strip depth) into *plan and launch nothing.
 hipError_t launch_mean9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
                         TileCfg cfg, hipStream_t s, TileCfg* plan = nullptr);
-// Whether a volume can be staged as element pairs: even row length and a base
-// address aligned to a pair of elements.
-inline bool mean9_pairs_ok(const void* base, int nx, size_t elem)
+// Whether rows are staged and stored as whole 32-bit words (WORDS in
+// mean9_tile.h).
+inline bool mean9_words_ok(const void* in, const void* out, int nx)
 {
-    return nx % 2 == 0 && reinterpret_cast<uintptr_t>(base) % (2 * elem) == 0;
+    return nx % 4 == 0 &&
+           (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 4 == 0;
+}
+
+// The tile ends a slice at a whole word, which a plane within 16 bytes of 4 GiB
+// (uint16, nx * ny >= 2^31 - 8) leaves no room for: such a volume runs on the
+// geometry kernel, which gives the same bytes.
+inline bool mean9_plane_ok(int dtype, Geom g)
+{
+    return dtype == LNF_U8 || (int64_t)g.nx * g.ny < (1ll << 31) - 8;
 }
 
 // ---- geometry variants (plane_tile.h): LNF_GEOM_* bits, both rules ---------
@@ -65,5 +77,7 @@ int default_zs(int tiles_xy, int nz, int target_groups);
 // Workgroups of `kernel` (launched with `threads` threads, no dynamic LDS) that
 // the current device holds at once: CUs x resident workgroups per CU.
 int resident_groups(const void* kernel, int threads);
+// CUs of the current device.
+int device_cus();
 
 }  // namespace lnf

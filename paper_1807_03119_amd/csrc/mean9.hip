@@ -9,10 +9,13 @@
 //   c   = ones on [-2r, 2r] plus one more at 0  (per axis, the two diagonal
 //         clusters at -r and +r overlap on the centre voxel; the product over
 //         the three axes enumerates the eight diagonal clusters).
-// The kernel evaluates it as separable running sums in exact uint32
-// arithmetic: per z-slice an x-pass and a y-pass through LDS, then a z-window
-// that slides through a register ring while the workgroup streams down its
-// z-strip.
+// The kernel evaluates the x- and y-axis as products with banded matrices on
+// the matrix cores, in exact arithmetic, and slides a z-window through a
+// register ring while each wavefront streams down its z-strip (mean9_tile.h).
+#include <algorithm>
+#include <climits>
+#include <vector>
+
 #include "device_common.h"
 #include "lnf_internal.h"
 #include "mean9_tile.h"
@@ -20,55 +23,37 @@
 namespace lnf {
 namespace {
 
-// Single-volume wrapper around the streaming tile body of mean9_tile.h.
-template <int R, int TY, typename T, bool GATE, int TXW>
-__global__ __launch_bounds__((M9Geo<R, TY, TXW>::THREADS))
-__attribute__((amdgpu_waves_per_eu((m9_waves<R, M9Geo<R, TY, TXW>::THREADS>())))) void mean9_stream(
+// Single-volume wrapper around the streaming tile body of mean9_tile.h.  BOX:
+// the paper's mean filter (eq. 4), the box term of the same tile.
+template <int R, int TY, typename T, bool GATE, int TXW, bool BOX>
+__global__ __launch_bounds__((M9Geo<R, TY, TXW, T>::THREADS))
+__attribute__((amdgpu_waves_per_eu((m9_waves<R, TY, T>())))) void mean9_stream(
     const T* __restrict__ in, T* __restrict__ out, Geom g, int zs, int tiles_x, int tiles_y,
-    int total, uint32_t gate, double inv9n, int pairs)
+    int total, uint32_t gate, double inv_div, int words)
 {
-    __shared__ __align__(16) M9SmemAny<R, TY, TXW, T> sm;
+    __shared__ __align__(16) M9Smem<R, TY, TXW, T> sm;
     const int tile = xcd_tile(blockIdx.x, total);
     const int bx = tile % tiles_x;
     const int rest = tile / tiles_x;
     const int by = rest % tiles_y;
     const int bz = rest / tiles_y;
     const int z0 = bz * zs;
-    mean9_tile<R, TY, T, GATE, TXW>(sm, pairs != 0, in, out, g, bx * TXW, by * TY, z0,
-                                    min(z0 + zs, g.nz), gate, inv9n, (int)threadIdx.x);
-}
-
-// The paper's mean filter (eq. 4): the box term of the same streaming tile,
-// 64 x 16 tiles.
-template <int R, typename T, bool GATE>
-__global__ __launch_bounds__((M9Geo<R, 16, 64>::THREADS))
-__attribute__((amdgpu_waves_per_eu((m9_waves<R, M9Geo<R, 16, 64>::THREADS>())))) void box_mean_stream(
-    const T* __restrict__ in, T* __restrict__ out, Geom g, int zs, int tiles_x, int tiles_y,
-    int total, uint32_t gate, double invn, int pairs)
-{
-    __shared__ __align__(16) M9SmemAny<R, 16, 64, T, true> sm;
-    const int tile = xcd_tile(blockIdx.x, total);
-    const int bx = tile % tiles_x;
-    const int rest = tile / tiles_x;
-    const int by = rest % tiles_y;
-    const int bz = rest / tiles_y;
-    const int z0 = bz * zs;
-    mean9_tile<R, 16, T, GATE, 64, true>(sm, pairs != 0, in, out, g, bx * 64, by * 16, z0,
-                                         min(z0 + zs, g.nz), gate, invn, (int)threadIdx.x);
+    mean9_tile<R, TY, T, GATE, TXW, BOX>(sm, words != 0, in, out, g, bx * TXW, by * TY, z0,
+                                         min(z0 + zs, g.nz), gate, inv_div, (int)threadIdx.x);
 }
 
 template <int R, typename T, bool GATE>
 hipError_t launch_box(const T* in, T* out, Geom g, uint32_t gate, hipStream_t s)
 {
-    constexpr int threads = M9Geo<R, 16, 64>::THREADS;
-    const auto kern = box_mean_stream<R, T, GATE>;
+    constexpr int threads = M9Geo<R, 16, 64, T>::THREADS;
+    const auto kern = mean9_stream<R, 16, T, GATE, 64, true>;
     const int tiles_x = (g.nx + 63) / 64, tiles_y = (g.ny + 15) / 16;
     const int zs = default_zs(tiles_x * tiles_y, g.nz, resident_groups((const void*)kern, threads));
     const int total = tiles_x * tiles_y * ((g.nz + zs - 1) / zs);
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
-    const int pairs = mean9_pairs_ok(in, g.nx, sizeof(T)) ? 1 : 0;
+    const int words = mean9_words_ok(in, out, g.nx) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(total), dim3(threads), 0, s, in, out, g, zs, tiles_x, tiles_y,
-                       total, gate, 1.0 / n, pairs);
+                       total, gate, 1.0 / n, words);
     return hipGetLastError();
 }
 
@@ -89,60 +74,125 @@ hipError_t dispatch_box(int r, const void* in, void* out, Geom g, uint32_t gate,
 struct Variant {
     int tx, ty, threads;
 };
-// output tiles of the compiled shapes: 64 or 32 wide, 16 or 32 high
-constexpr Variant kVariants[] = {{64, 16, 256}, {64, 32, 512}, {32, 16, 128}, {32, 32, 256}};
+// output tiles of the compiled shapes
+constexpr Variant kVariants[] = {{64, 16, 256}, {128, 32, 512}, {32, 16, 128}, {128, 16, 512}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-// Default variant per voxel type and radius (index r-1): the fastest at the
-// default z-strip depth on 512^3 volumes (uint16 r = 1: 32 x 16 tiles, about
-// 1080 against 960 Gvoxel/s for 64 x 16; uint8 r = 4: 64 x 16, about 690
-// against 620 for 32 x 32).
-constexpr int kDefaultU16[LNF_RADIUS_MAX] = {2, 0, 0, 3};
-constexpr int kDefaultU8[LNF_RADIUS_MAX] = {0, 0, 0, 0};
+// Costs are kept for rows that are staged and stored as whole words (nx a
+// multiple of 4) and for others, whose stores go voxel by voxel.
+// The default tile is the variant and strip depth with the least estimated
+// time: rounds of resident workgroups x iterations of a strip x time of an
+// iteration.  Iterations come in whole blocks of 2r+2 and include the 4r
+// slices of z-halo, the two of the pipeline.  Times of an iteration (10 ns)
+// with one workgroup on a CU, and for each further one, measured on 64^3 to
+// 512^3 volumes: the wide tiles move the least halo and win where a volume has
+// a strip for every CU (512^3, r = 3, uint16: 128 x 32 123 us, 128 x 16 133,
+// 64 x 16 168, 32 x 16 248; uint8 69, 81, 106, 176); below that the narrow
+// ones do (64^3 uint16: 32 x 16 10.3 us, 64 x 16 11.4, 128 x 32 22).  The
+// 128 x 32 tile of uint16 at r = 4 spills registers and is not chosen.
+struct TileCost {
+    int one, more, resident;
+};
+constexpr TileCost kCostU16[2][kNumVariants] = {{{38, 22, 3}, {116, 0, 1}, {36, 12, 6}, {66, 0, 1}},
+                                                {{36, 20, 3}, {84, 0, 1}, {33, 12, 6}, {50, 0, 1}}};
+constexpr TileCost kCostU8[2][kNumVariants] = {{{30, 16, 4}, {74, 0, 1}, {28, 8, 8}, {44, 20, 2}},
+                                               {{28, 14, 4}, {48, 0, 1}, {26, 8, 8}, {36, 20, 2}}};
+// At r = 4 the rings take more registers, so fewer workgroups are resident.
+constexpr int kResidentU16R4[kNumVariants] = {2, 1, 4, 1}, kResidentU8R4[kNumVariants] = {3, 1, 6, 1};
+
+TileCost cost_of(int dtype, int variant, int r, Geom g)
+{
+    const int words = g.nx % 4 == 0;
+    TileCost c = dtype == LNF_U8 ? kCostU8[words][variant] : kCostU16[words][variant];
+    if (r == 4) c.resident = dtype == LNF_U8 ? kResidentU8R4[variant] : kResidentU16R4[variant];
+    return c;
+}
+
+long long tile_groups(int variant, int zs, Geom g)
+{
+    const Variant v = kVariants[variant];
+    return (long long)((g.nx + v.tx - 1) / v.tx) * ((g.ny + v.ty - 1) / v.ty) * ((g.nz + zs - 1) / zs);
+}
+
+int tile_iterations(int zs, int r)
+{
+    const int d = 2 * r + 2;
+    return (zs + 4 * r + 2 + d - 1) / d * d;
+}
+
+// Whether `variant` is one to consider when `want` is asked for.
+bool tile_eligible(int variant, int want, int dtype, int r)
+{
+    if (want >= 0 && want < kNumVariants) return variant == want;
+    return !(variant == 1 && r == 4 && dtype == LNF_U16);
+}
+
+// variant < 0 and zs <= 0 ask for the default.
+TileCfg resolve_tile(TileCfg want, int dtype, int r, Geom g)
+{
+    TileCfg best = want;
+    int best_cost = INT_MAX;
+    const int cus = device_cus(), most = std::max(1, g.nz / 4);  // strips of 4 slices at least
+    for (int v = 0; v < kNumVariants; ++v) {
+        if (!tile_eligible(v, want.variant, dtype, r)) continue;
+        const TileCost c = cost_of(dtype, v, r, g);
+        const int cols = (int)std::min<long long>(tile_groups(v, g.nz, g), 1 << 24);
+        // strip counts that fill whole rounds: one round of 1 .. resident
+        // workgroups per CU, or up to four full ones
+        for (int i = 1; i < c.resident + 4; ++i) {
+            const int per_cu = std::min(i, c.resident), rounds = i - per_cu + 1;
+            int nzs = want.zs > 0 ? (g.nz + want.zs - 1) / want.zs
+                                  : std::min(most, std::max(1, cus * per_cu * rounds / cols));
+            const int zs = want.zs > 0 ? want.zs : (g.nz + nzs - 1) / nzs;
+            nzs = (g.nz + zs - 1) / zs;
+            const int groups = (int)std::min<long long>((long long)cols * nzs, 1 << 30);
+            const int n = std::min(c.resident, (groups + cus - 1) / cus);
+            const double cost = (double)((groups + cus * n - 1) / (cus * n)) * tile_iterations(zs, r) *
+                                (c.one + (n - 1) * c.more);
+            if (cost < best_cost) {
+                best_cost = (int)std::min(cost, 2e9);
+                best = TileCfg{v, zs};
+            }
+        }
+    }
+    return best;
+}
 
 template <int R, typename T, bool GATE, int TY, int TXW>
-hipError_t launch_stream(const T* in, T* out, Geom g, uint32_t gate, int zs, hipStream_t s,
-                         TileCfg* plan)
+hipError_t launch_stream(const T* in, T* out, Geom g, uint32_t gate, int zs, hipStream_t s)
 {
-    constexpr int threads = M9Geo<R, TY, TXW>::THREADS;
-    const auto kern = mean9_stream<R, TY, T, GATE, TXW>;
+    constexpr int threads = M9Geo<R, TY, TXW, T>::THREADS;
+    const auto kern = mean9_stream<R, TY, T, GATE, TXW, false>;
     const int tiles_x = (g.nx + TXW - 1) / TXW, tiles_y = (g.ny + TY - 1) / TY;
-    // default z-strip depth: one full round of resident workgroups
-    if (zs <= 0)
-        zs = default_zs(tiles_x * tiles_y, g.nz, resident_groups((const void*)kern, threads));
-    if (plan) {
-        plan->zs = zs;
-        return hipSuccess;
-    }
     const int nzs = (g.nz + zs - 1) / zs;
     const int total = tiles_x * tiles_y * nzs;
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
-    const int pairs = mean9_pairs_ok(in, g.nx, sizeof(T)) ? 1 : 0;
+    const int words = mean9_words_ok(in, out, g.nx) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(total), dim3(threads), 0, s, in, out, g, zs, tiles_x, tiles_y,
-                       total, gate, 1.0 / (9.0 * n), pairs);
+                       total, gate, 1.0 / (9.0 * n), words);
     return hipGetLastError();
 }
 
 template <int R, typename T, bool GATE>
 hipError_t launch_variant(int variant, const void* in, void* out, Geom g, uint32_t gate, int zs,
-                          hipStream_t s, TileCfg* plan)
+                          hipStream_t s)
 {
     const T* pin = static_cast<const T*>(in);
     T* pout = static_cast<T*>(out);
     switch (variant) {
-    case 0: return launch_stream<R, T, GATE, 16, 64>(pin, pout, g, gate, zs, s, plan);
-    case 1: return launch_stream<R, T, GATE, 32, 64>(pin, pout, g, gate, zs, s, plan);
-    case 2: return launch_stream<R, T, GATE, 16, 32>(pin, pout, g, gate, zs, s, plan);
-    default: return launch_stream<R, T, GATE, 32, 32>(pin, pout, g, gate, zs, s, plan);
+    case 0: return launch_stream<R, T, GATE, 16, 64>(pin, pout, g, gate, zs, s);
+    case 1: return launch_stream<R, T, GATE, 32, 128>(pin, pout, g, gate, zs, s);
+    case 2: return launch_stream<R, T, GATE, 16, 32>(pin, pout, g, gate, zs, s);
+    default: return launch_stream<R, T, GATE, 16, 128>(pin, pout, g, gate, zs, s);
     }
 }
 
 template <int R, typename T>
 hipError_t launch_r(int variant, const void* in, void* out, Geom g, uint32_t gate, int zs,
-                    hipStream_t s, TileCfg* plan)
+                    hipStream_t s)
 {
-    if (gate) return launch_variant<R, T, true>(variant, in, out, g, gate, zs, s, plan);
-    return launch_variant<R, T, false>(variant, in, out, g, gate, zs, s, plan);
+    if (gate) return launch_variant<R, T, true>(variant, in, out, g, gate, zs, s);
+    return launch_variant<R, T, false>(variant, in, out, g, gate, zs, s);
 }
 
 template <typename T>
@@ -150,15 +200,17 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
                       hipStream_t s, TileCfg* plan)
 {
     if (r < 1 || r > LNF_RADIUS_MAX) return hipErrorInvalidValue;
-    const int v = (cfg.variant >= 0 && cfg.variant < kNumVariants)
-                      ? cfg.variant
-                      : mean9_default_variant(sizeof(T) == 1 ? LNF_U8 : LNF_U16, r);
-    if (plan) plan->variant = v;
+    cfg = resolve_tile(cfg, sizeof(T) == 1 ? LNF_U8 : LNF_U16, r, g);
+    if (plan) {
+        *plan = cfg;
+        return hipSuccess;
+    }
+    const int v = cfg.variant;
     switch (r) {
-    case 1: return launch_r<1, T>(v, in, out, g, gate, cfg.zs, s, plan);
-    case 2: return launch_r<2, T>(v, in, out, g, gate, cfg.zs, s, plan);
-    case 3: return launch_r<3, T>(v, in, out, g, gate, cfg.zs, s, plan);
-    default: return launch_r<4, T>(v, in, out, g, gate, cfg.zs, s, plan);
+    case 1: return launch_r<1, T>(v, in, out, g, gate, cfg.zs, s);
+    case 2: return launch_r<2, T>(v, in, out, g, gate, cfg.zs, s);
+    case 3: return launch_r<3, T>(v, in, out, g, gate, cfg.zs, s);
+    default: return launch_r<4, T>(v, in, out, g, gate, cfg.zs, s);
     }
 }
 
@@ -166,10 +218,35 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
 
 int mean9_variants() { return kNumVariants; }
 
-int mean9_default_variant(int dtype, int r)
+TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>& g)
 {
-    r = r < 1 ? 1 : r > LNF_RADIUS_MAX ? LNF_RADIUS_MAX : r;
-    return dtype == LNF_U8 ? kDefaultU8[r - 1] : kDefaultU16[r - 1];
+    constexpr int kDepths[] = {16, 24, 32, 48, 64, 96, 128, 192};
+    TileCfg best{0, 16};
+    float best_cost = -1.f;
+    const float cus = (float)device_cus();
+    for (int v = 0; v < kNumVariants; ++v) {
+        if (!tile_eligible(v, variant, dtype, r)) continue;
+        float work[8] = {}, longest[8] = {};
+        for (const Geom& q : g) {
+            const TileCost c = cost_of(dtype, v, r, q);
+            const float tau = (float)(c.one + (c.resident - 1) * c.more);
+            const float cols = (float)tile_groups(v, q.nz, q) * tau / c.resident;
+            for (int i = 0; i < 8; ++i) {
+                const int nzs = (q.nz + kDepths[i] - 1) / kDepths[i];
+                const float iters = (float)tile_iterations((q.nz + nzs - 1) / nzs, r);
+                work[i] += cols * nzs * iters;
+                longest[i] = std::max(longest[i], tau * iters);
+            }
+        }
+        for (int i = 0; i < 8; ++i) {
+            const float cost = work[i] / cus + longest[i];  // and a tail of the longest strip
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
+                best = TileCfg{v, kDepths[i]};
+            }
+        }
+    }
+    return best;
 }
 
 void mean9_tile_shape(int variant, int* tx, int* ty)
@@ -189,6 +266,8 @@ hipError_t launch_box_mean(const void* in, void* out, int dtype, int r, Geom g, 
 hipError_t launch_mean9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
                         TileCfg cfg, hipStream_t s, TileCfg* plan)
 {
+    if (!plan && !mean9_plane_ok(dtype, g))
+        return launch_geometry(LNF_MEAN9, 0, in, out, dtype, r, g, gate, cfg.zs, s);
     if (dtype == LNF_U8) return dispatch_r<uint8_t>(in, out, r, g, gate, cfg, s, plan);
     return dispatch_r<uint16_t>(in, out, r, g, gate, cfg, s, plan);
 }

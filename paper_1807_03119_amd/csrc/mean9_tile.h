@@ -1,464 +1,413 @@
-// Streaming MEAN9 tile body: one workgroup filters a TX x TY column of output
+// Streaming MEAN9 tile body: one workgroup filters a TXW x TY column of output
 // voxels over the z-range [z0, z1).  Shared by the single-volume kernel, the
 // mean filter and the batch kernel.
 //
 // Arithmetic (paper, Section "Our Method", eqs. 2-3): the sum S over the nine
 // clusters is box_x box_y box_z E + c_x c_y c_z E, with box = ones on [-r, r]
-// and c = ones on [-2r, 2r] plus one more at the centre (the two diagonal
-// clusters of an axis overlap there).  Per axis c = box shifted by -r plus box
-// shifted by +r.  Everything is exact uint32.
-//
-// Per input slice s the x- and y-passes give the plane sums
+// and c = box shifted by -r plus box shifted by +r (the two diagonal clusters
+// of an axis).  Per input slice s the x- and y-passes give the plane sums
 //   P(s) = box_y box_x E(s),   Q(s) = c_y c_x E(s)
-// at each output column.  Along z, c_z = box_z shifted by -r plus by +r, so
-//   S(z) = sum_{t=z-r..z+r} P(t) + sum_{t=z-r..z+r} Q(t-r) + sum_{t=z-r..z+r} Q(t+r)
-//        = sum_{t=z..z+2r} G(t),   G(t) = P(t-r) + Q(t) + Q(t-2r),
-// a running box of 2r+1 slices of one quantity.  A value of P is kept r
-// slices, of Q 2r slices and of G 2r+1 slices: 5r+1 registers per output
-// column, in a register ring of D = 2r+2 slots indexed statically by the
-// unrolled loop (the allocator keeps only the live values).
+// at each output column, and along z
+//   S(z) = sum_{t=z..z+2r} G(t),   G(t) = P(t-r) + Q(t) + Q(t-2r).
 //
-// Pipeline per iteration k (one barrier per iteration):
-//   - LDS reads of this thread's raw row segment of slice k and of its x-pass
-//     column of slice k-1;
-//   - y-pass of slice k-1 (each thread owns one column and YO = 4 rows; prefix
-//     sums), G, the running sum, out = round(S / 9n) (fp64, exact), gate and
-//     the stores of output slice k-1-4r;
-//   - LDS DMA of the raw (TX+4r) x (TY+4r) tile of slice k+PF straight from
-//     HBM into LDS, coordinates clamped into the volume per lane; NRB = PF+1
-//     raw buffers form a ring, so each slice has PF iterations to arrive;
-//   - x-pass of slice k: each thread takes an 8-wide row segment and forms
-//     px = box_x E and qx = c_x E from prefix sums over its 8+4r raw values.
-// The x-pass results are double-buffered, so the x-pass of slice k overlaps
-// the y-pass of slice k-1.  Every iteration issues exactly NLOAD loads and YO
-// stores (masked-off stores go to an offset the buffer's range check drops),
-// so the wait for slice k+1 at the end of iteration k is a partial one that
-// leaves the younger PF-1 iterations' operations in flight.
-//
-// Modes:
-//   kM9Packed  px <= qx, and when qx < 2^16 both fit one LDS word px | qx<<16.
-//              The x-pass stores half as much and a y-pass thread loads 4+4r
-//              words instead of (4+2r) + (4+4r): its px rows lie inside its qx
-//              rows.  Whether qx < 2^16 depends on the data (always for values
-//              up to 65535 / (4r+2): uint8, or 12-bit data up to r = 3), so
-//              the x-pass ORs together every qx it forms; at the end of each
-//              block of D slices the workgroup checks the OR, and a tile that
-//              saw qx >= 2^16 stops: the caller filters it again in kM9Exact
-//              from the first output slice that may hold a wrong value on.
-//              Exact for every input.
-//   kM9Exact   px and qx in separate uint32 LDS words.
-//   kM9Box     the box term alone (the paper's mean filter, eq. 4): px only,
-//              S(z) = sum_{t=z-r..z+r} P(t).
+// The x- and y-passes are products with banded matrices, and run on the matrix
+// cores.  One wavefront computes 16 columns x 16*NO rows of outputs; TXW / 16
+// of them, side by side, share the staged rows of a slice.
+//   1. staging.  The 32 columns [x-8, x+24) around a 16-column block hold its
+//      window for every r <= 4, as do 32 rows.  The rows of a slice go to LDS
+//      in 16-byte chunks, by LDS DMA (buffer_load ... lds, 16 bytes per lane)
+//      PF slices ahead; rows are clamped by their address.  In x the chunks
+//      just run on past the row: what is outside the volume has no weight, and
+//      the range check of the buffer resource ends the slice.
+//   2. digits.  f16 holds integers up to 2048 exactly and the products
+//      accumulate in fp32, exact below 2^24.  A voxel is split into bytes
+//      (uint16: low and high): one byte permute forms two f16 1024 + byte, and
+//      the accumulator of the x-pass starts at -1152 * (sum of the weights),
+//      so that the sums are those of byte - 128.  Window sums of a digit are
+//      at most 128 (4r+2), 1792 at r = 3; at r = 4 the c-sum would reach 2304,
+//      so it is kept as its two boxes.
+//   3. x-pass: D1[row][col] = sum_k raw[row][k] Wx[k][col], 16x16x32 products
+//      whose A operand is one 16-byte LDS read per lane (row = lane % 16,
+//      chunk lane / 16).  The weights of samples outside the volume are folded
+//      onto the face voxel that they clamp to.
+//   4. y-pass: a lane of D1 holds four consecutive rows of one column, so the
+//      D1 of two row blocks are, converted to f16, the A operand of the
+//      transposed product D2[col][row] = sum_k D1[k][col] Wy[k][row] with k in
+//      the order that the registers have: no exchange between the passes.
+//      uint16: the high digit's weights are 256-fold and chained onto the low
+//      digit's sum; |D2| <= 324 * 32896 < 2^24.
+//   5. z-pass in registers: V(t) = P(t) + Q(t-r), G(t) = Q(t) + V(t-r), a
+//      running box of G over 2r+1 slices: 4r+2 values per output, in rings
+//      indexed statically by the unrolled loop (uint32 arithmetic modulo 2^32
+//      for uint16; uint8 sums stay below 2^24 and are kept in fp32).
+//   6. out = round(S / 9n), gate.  A lane holds four consecutive columns of one
+//      row, so the outputs pass through LDS and are stored, one slice later,
+//      with 16 adjacent lanes to a row.
+// One LDS barrier a slice: iteration k computes slice k, starts the staging of
+// slice k+PF and stores the outputs of iteration k-1.
+// Everything is exact: the same bytes as the definition for every input.
 #pragma once
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "lnf_internal.h"
 
 namespace lnf {
 
-constexpr int kM9Exact = 0, kM9Packed = 1, kM9Box = 2;
+using half4_t = _Float16 __attribute__((ext_vector_type(4)));
+using half8_t = _Float16 __attribute__((ext_vector_type(8)));
+using f32x4_t = float __attribute__((ext_vector_type(4)));
+using u32x4_t = uint32_t __attribute__((ext_vector_type(4)));
 
-// Tile geometry.  PK: the raw tile is staged as element pairs, one 32-bit LDS
-// word per pair (uint16: both halves; uint8: the low two bytes), loaded by one
-// LDS DMA per lane.  That halves the DMA instructions and the LDS bytes of the
-// staging and of the x-pass reads.  It needs an even nx (pairs never straddle
-// a row end), a volume base aligned to a pair, and a tile whose halo stays
-// inside the volume in x (a pair cannot be clamped element by element); tiles
-// at an x face are staged element-wise.
-template <int R, int TY, int TXW = 64, bool PK = false>
+// Tile geometry: TXW / 16 wavefronts side by side, NO = TY / 16 row blocks each.
+template <int R, int TY, int TXW, typename T>
 struct M9Geo {
-    static constexpr int TX = TXW;
-    static constexpr int YO = 4;                    // output rows per thread
-    static constexpr int THREADS = TX * TY / YO;    // one thread per column x YO rows
-    static constexpr int H = 2 * R;                 // halo: cluster radius + offset
-    static constexpr int EPW = PK ? 2 : 1;          // raw elements per LDS word
-    static constexpr int LXE = TX + 4 * R;          // raw elements per tile row
-    static constexpr int LXW = LXE / EPW;           // LDS words holding them (LXE even)
-    // Raw row pitch in words: padded to 4 mod 8, so that eight consecutive
-    // rows start in eight different groups of four LDS banks (the x-pass reads
-    // 16 bytes per lane, eight lanes per bank cycle).  The padding words repeat
-    // the row's last word and are never used.
-    static constexpr int LX = LXW + (12 - LXW % 8) % 8;
-    static constexpr int LY = TY + 2 * H;
-    static constexpr int NRAW = LX * LY;            // staged words per slice
-    static constexpr int NLOAD = (NRAW + THREADS - 1) / THREADS;
-    static constexpr int RAWW = NLOAD * THREADS;    // words of one raw buffer
-    static constexpr int PXP = TX + 4;              // padded x-pass row pitch (words)
-    static constexpr int XPW = (LY + 1) * PXP;      // words of one x-pass buffer
-    static constexpr int D = 2 * R + 2;             // ring period and unroll (even)
-    static constexpr int SEG = 8, NSEG = TX / SEG, SW = SEG + 4 * R;
-    static constexpr int SWW = SW / EPW;            // words an x-pass segment reads
-    static constexpr int XR = (LY + 7) / 8 * 8;     // x-pass row slots (multiple of 8)
-    static constexpr int NPV = YO + 2 * R, NQV = YO + 4 * R;
-    static_assert(XR * NSEG <= THREADS, "x-pass: one thread per row segment");
-    static_assert(D % 2 == 0, "buffer parity must be static in the unrolled ring");
-    static_assert(LX % 4 == 0 && (SEG / EPW) % 4 == 0, "x-pass reads 16-byte aligned rows");
-    static_assert(SWW % 2 == 0 && LXE % 2 == 0, "x-pass reads whole 8-byte pieces");
+    static constexpr int THREADS = TXW / 16 * 64;
+    static constexpr int NO = TY / 16;         // 16-row output blocks
+    static constexpr int NR = NO + 1;          // 16-row raw blocks
+    static constexpr int LY = TY + 4 * R;      // staged rows
+    static constexpr int CV = 16 / sizeof(T);  // voxels of a chunk
+    // Staged chunks per row: one left of the tile, and past it 8 columns and
+    // the word that an unaligned row is shifted by; odd, so that eight rows of a
+    // 16-byte read start in eight different groups of four banks.
+    static constexpr int NC = ((TXW + CV + 8) / CV + 1) | 1;
+    static constexpr int NCH = LY * NC;        // chunks per slice
+    static constexpr int NLOAD = (NCH + THREADS - 1) / THREADS;
+    static constexpr int D = 2 * R + 2;        // ring period and unroll (even)
+    // raw slices in LDS: a divisor of the unroll, so that a slice's buffer is static
+    static constexpr int NRB = R == 4 ? 5 : R == 2 ? 3 : 4;
+    static constexpr int PF = NRB - 1;         // slices staged ahead
+    static_assert(TXW % 16 == 0 && TY % 16 == 0 && R <= 4 && D % NRB == 0, "tile shape");
 };
 
-// LDS one workgroup may use: three 256-thread workgroups per CU (160 KiB).
-constexpr int kM9LdsBudget = 53 * 1024;
-
-// Waves per SIMD the tile kernels are compiled for: three up to r = 3 (the
-// tile body fits 168 VGPRs there), two at r = 4 and for 512-thread
-// workgroups (one of those per CU holds two waves per SIMD).
-template <int R, int THREADS>
+// Waves per SIMD the tile kernels are compiled for: as many as the registers
+// allow without spills.
+template <int R, int TY, typename T>
 constexpr int m9_waves()
 {
-    return (R <= 3 && THREADS <= 256) ? 3 : 2;
+    if (TY == 32) return 2;
+    return sizeof(T) == 1 ? (R <= 3 ? 4 : 3) : (R <= 3 ? 3 : 2);
 }
 
-template <int R, int TY, int TXW, bool PK, int MODE>
-struct M9Shape : M9Geo<R, TY, TXW, PK> {
-    using G = M9Geo<R, TY, TXW, PK>;
-    static constexpr int XBUFS = MODE == kM9Exact ? 4 : 2;  // px (and qx), double-buffered
-    static constexpr int bytes_for(int nrb) { return 4 * (XBUFS * G::XPW + nrb * G::RAWW) + 16; }
-    // Raw buffers: the largest count up to 5 that divides the unroll (so a
-    // slice's buffer index is static), keeps the partial wait within the 6-bit
-    // counter and fits the budget (the least, 2, if none does).
-    static constexpr int pick_nrb()
-    {
-        for (int n = 5; n > 2; --n)
-            if (G::D % n == 0 && (n - 2) * (G::NLOAD + G::YO) <= 63 &&
-                bytes_for(n) <= kM9LdsBudget)
-                return n;
-        return 2;
-    }
-    static constexpr int NRB = pick_nrb();
-    static constexpr int PF = NRB - 1;  // slices staged ahead of the x-pass
-    // vector-memory operations issued after a slice's loads, up to the wait
-    // that needs that slice: PF-1 iterations of (NLOAD loads + YO stores)
-    static constexpr int VMWAIT = (PF - 1) * (G::NLOAD + G::YO);
-    static_assert(G::D % NRB == 0 && VMWAIT <= 63, "raw ring");
-};
-
-template <int R, int TY, int TXW, bool PK, int MODE>
+template <int R, int TY, int TXW, typename T>
 struct M9Smem {
-    using S = M9Shape<R, TY, TXW, PK, MODE>;
-    uint32_t raw[S::NRB][S::RAWW];
-    // x-pass results; the extra row LY takes the surplus x-pass lanes' stores,
-    // so no two lanes of a store hit the same address
-    uint32_t px[2][S::XPW];
-    uint32_t qx[MODE == kM9Exact ? 2 : 1][MODE == kM9Exact ? S::XPW : 1];
-    uint32_t flag;  // kM9Packed: some x-pass of the tile formed qx >= 2^16
+    using G = M9Geo<R, TY, TXW, T>;
+    u32x4_t raw[G::NRB][G::NLOAD * G::THREADS];
+    T outs[2][TY][TXW + 16];  // pitch: the rows of a store fall in different banks
 };
 
-// Whether packed mode can see qx >= 2^16 for this element type and radius.
-template <typename T, int R>
-constexpr bool m9_packed_may_overflow()
+// WORDS: nx is a multiple of 4 and both volumes start at multiples of 4 bytes,
+// so rows are staged as they are and four outputs of a row stored as whole
+// words.  Otherwise a row is staged from the aligned word that holds its first
+// byte on and shifted as it is read, and outputs are stored one by one.
+// inv_div: 1/(9n), or 1/n with BOX (the box term alone: the mean filter).
+template <int R, int TY, typename T, bool GATE, int TXW, bool BOX, bool WORDS>
+__device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* __restrict__ in,
+                                           T* __restrict__ out, Geom g, int x0, int y0, int z0,
+                                           int z1, uint32_t gate, double inv_div, int tid)
 {
-    return (uint64_t)(4 * R + 2) * ((1u << (8 * sizeof(T))) - 1u) >= 65536u;
-}
+    using S = M9Geo<R, TY, TXW, T>;
+    constexpr int NO = S::NO, NR = S::NR, D = S::D, NC = S::NC, NLOAD = S::NLOAD, CV = S::CV;
+    constexpr int kT = S::THREADS, NRB = S::NRB, PF = S::PF;
+    constexpr int DIG = sizeof(T);               // digits (bytes) per voxel
+    constexpr bool SPLIT = !BOX && R == 4;       // c-sum as its two boxes
+    constexpr int NQ = BOX ? 1 : SPLIT ? 3 : 2;  // x-pass quantities: P, then Q (or its halves)
+    constexpr int LAG = BOX ? 2 * R : 4 * R;     // input slices before the first output
+    constexpr int ZH = BOX ? R : 2 * R;          // z-halo of the strip
+    constexpr float kBias = sizeof(T) == 1 ? 128.f : 32896.f;
+    constexpr bool FP = sizeof(T) == 1;          // z-sums in fp32
+    using Z = std::conditional_t<FP, float, uint32_t>;
 
-// inv_div: 1/(9n), or 1/n with kM9Box.  Returns z1 when every output slice
-// of [z0, z1) is final.  A kM9Packed tile that stopped because some qx did
-// not fit 16 bits returns the first output slice that may be wrong instead:
-// the slices before it are final, and the rest must be filtered again in
-// kM9Exact from that slice on.
-template <int R, int TY, typename T, bool GATE, int TXW, bool PK, int MODE>
-__device__ __forceinline__ int mean9_tile_body(M9Smem<R, TY, TXW, PK, MODE>& sm,
-                                                const T* __restrict__ in, T* __restrict__ out,
-                                                Geom g, int x0, int y0, int z0, int z1,
-                                                uint32_t gate, double inv_div, int tid)
-{
-    using S = M9Shape<R, TY, TXW, PK, MODE>;
-    constexpr bool kBox = MODE == kM9Box, kPQ = MODE == kM9Packed;
-    constexpr bool kCheck = kPQ && m9_packed_may_overflow<T, R>();
-    constexpr int H = S::H, LX = S::LX, D = S::D, TX = S::TX, PXP = S::PXP, YO = S::YO;
-    constexpr int EPW = S::EPW, NRB = S::NRB, PF = S::PF;
-    // output slice of iteration k: z0 + k - 1 - LAG
-    constexpr int LAG = kBox ? 3 * R : 4 * R;
-    // wave index as a scalar, so the LDS DMA destinations are scalar arithmetic
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t plane = (size_t)g.nx * g.ny;
+    const int l = tid & 15, gq = (tid >> 4) & 3;
+    const int nx = g.nx, ny = g.ny;
+    const size_t plane = (size_t)nx * ny;
     const uint32_t pbytes = (uint32_t)(plane * sizeof(T));
 
-    // byte offsets (within a slice) of the raw words this lane stages
-    uint32_t off[S::NLOAD];
+    // ---- staging: slot tid + i * kT of a buffer holds chunk slot % NC of row
+    // slot / NC; lanes past the tile repeat the last slot's.  off: its byte
+    // offset in a slice; only chunks outside the volume start before the slice,
+    // and they are moved to its start.
+    const int xl = x0 - CV;  // first staged column
+    uint32_t off[NLOAD];
 #pragma unroll
-    for (int i = 0; i < S::NLOAD; ++i) {
-        const int e = min(tid + i * S::THREADS, S::NRAW - 1);
-        const int row = e / LX;
-        // padding words re-read the row's last word: no extra cache lines
-        const int col = min(e - row * LX, S::LXW - 1);
-        const int gy = clampi(y0 - H + row, 0, g.ny - 1);
-        const int gx = clampi(x0 - H + EPW * col, 0, g.nx - EPW);  // even when PK
-        off[i] = (uint32_t)(gy * g.nx + gx) * (uint32_t)sizeof(T);
+    for (int i = 0; i < NLOAD; ++i) {
+        const int e = min(tid + i * kT, S::NCH - 1);
+        const int row = e / NC, c = e - row * NC;
+        const int64_t at = (int64_t)clampi(y0 - 2 * R + row, 0, ny - 1) * nx + xl + CV * c;
+        off[i] = (uint32_t)(max(at, (int64_t)0) * (int)sizeof(T));
     }
-    // every lane issues all NLOAD loads (lanes past the tile reload its last
-    // word into unused LDS words), so the count per stage is fixed
-    auto stage = [&](int zi, int slot) {
-        const rsrc_t rs = make_rsrc(in + (size_t)clampi(zi, 0, g.nz - 1) * plane, pbytes);
+    // the next slice to load, clamped into the volume
+    int zl = z0 - ZH;
+    const T* lp = in + (size_t)clampi(zl, 0, g.nz - 1) * plane;
+    auto stage = [&](int buf) {  // the next slice into buffer buf
+        const uint32_t lead = WORDS ? 0u : (uint32_t)(reinterpret_cast<uintptr_t>(lp) & 3);
+        const rsrc_t rs = make_rsrc(reinterpret_cast<const char*>(lp) - lead, WORDS ? pbytes : (min(pbytes, 0xfffffff8u) + lead + 3) & ~3u);
 #pragma unroll
-        for (int i = 0; i < S::NLOAD; ++i) {
-            if constexpr (PK)
-                buffer_load_lds_pair<T>(rs, &sm.raw[slot][i * S::THREADS + wave * 64], off[i]);
+        for (int i = 0; i < NLOAD; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (lds_void_t*)&sm.raw[buf][i * kT + wave * 64], 16,
+                WORDS ? off[i] : (off[i] + lead) & ~3u, 0, 0, 0);
+        lp += (zl >= 0 && zl < g.nz - 1) ? plane : 0;
+        ++zl;
+    };
+
+    // ---- x-pass weights of output column x0 + 16 wave + l: how often its
+    // window samples column x0 - 8 + 16 wave + 8 gq + j, the voxel of k-slot
+    // (gq, j); clamped samples count at the faces, columns outside nothing
+    half8_t wx[NQ];
+    {
+        const int xc = x0 + 16 * wave + l;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int c = x0 - 8 + 16 * wave + 8 * gq + j;
+            const bool mine = c >= 0 && c < nx;
+            auto box = [&](int ctr) {
+                const int hi = c >= nx - 1 ? 2 * R + 1 : clampi(c - (ctr - R) + 1, 0, 2 * R + 1);
+                const int lo = c <= 0 ? 0 : clampi(c - (ctr - R), 0, 2 * R + 1);
+                return mine ? hi - lo : 0;
+            };
+            wx[0][j] = (_Float16)(float)box(xc);
+            if constexpr (SPLIT) {
+                wx[1][j] = (_Float16)(float)box(xc - R);
+                wx[2][j] = (_Float16)(float)box(xc + R);
+            } else if constexpr (!BOX) {
+                wx[1][j] = (_Float16)(float)(box(xc - R) + box(xc + R));
+            }
+        }
+    }
+    // ---- y-pass weights of output row l of a block over the 32 raw rows from
+    // 8 above the block; k-slot (gq, j) is row 4 gq + j of the upper raw block
+    // for j < 4, row 4 gq + j - 4 of the lower one from there
+    half8_t wyp[DIG], wyq[DIG];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int d = (j < 4 ? 4 * gq + j : 16 + 4 * gq + j - 4) - 8 - l;
+        const int p = (d >= -R && d <= R) ? 1 : 0;
+        const int q = ((d >= -2 * R && d <= 0) ? 1 : 0) + ((d >= 0 && d <= 2 * R) ? 1 : 0);
+#pragma unroll
+        for (int t = 0; t < DIG; ++t) {
+            wyp[t][j] = (_Float16)(float)(t ? 256 * p : p);
+            wyq[t][j] = (_Float16)(float)(t ? 256 * q : q);
+        }
+    }
+    // ---- A operands: raw row block rt holds rows y0 - 8 + 16 rt + l, staged
+    // from y0 - 2R on; rows outside have no weight and read a staged one
+    int aoff[NR];       // byte offset in a buffer
+    uint32_t arow[NR];  // byte offset of the staged row in its slice (modulo 4)
+#pragma unroll
+    for (int rt = 0; rt < NR; ++rt) {
+        const int row = clampi(16 * rt + l - 8 + 2 * R, 0, S::LY - 1);
+        aoff[rt] = row * NC * 16 + (CV - 8 + 8 * (2 * wave + gq)) * (int)sizeof(T);
+        arow[rt] = ((uint32_t)clampi(y0 - 2 * R + row, 0, ny - 1) * (uint32_t)nx + (uint32_t)xl) * (uint32_t)sizeof(T);
+    }
+    // the slice read, clamped as staged, and its bytes past an aligned word
+    int zr = z0 - ZH;
+    uint32_t rlead = (uint32_t)(reinterpret_cast<uintptr_t>(lp) & 3);
+    using words_t = uint32_t __attribute__((ext_vector_type(2 * sizeof(T))));
+    auto read_raw = [&](int buf, int rt) -> words_t {
+        const char* p = reinterpret_cast<const char*>(sm.raw[buf]) + aoff[rt];
+        words_t w = *reinterpret_cast<const words_t*>(p);
+        if constexpr (!WORDS) {
+            constexpr int kN = 2 * sizeof(T);
+            const uint32_t more = *reinterpret_cast<const uint32_t*>(p + 4 * kN), by = arow[rt] + rlead;
+#pragma unroll
+            for (int a = 0; a < kN; ++a)
+                w[a] = __builtin_amdgcn_alignbyte(a + 1 < kN ? w[a + 1] : more, w[a], by);
+        }
+        return w;
+    };
+    auto operand = [&](const words_t& w, int t) -> half8_t {  // 1024 + byte t of 8 voxels
+        u32x4_t d;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            if constexpr (sizeof(T) == 2)
+                d[a] = __builtin_amdgcn_perm(0x64646464u, w[a], t ? 0x04030401u : 0x04020400u);
             else
-                buffer_load_lds<T>(rs, &sm.raw[slot][i * S::THREADS + wave * 64], off[i]);
+                d[a] = __builtin_amdgcn_perm(0x64646464u, w[a / 2], (a & 1) ? 0x04030402u : 0x04010400u);
         }
+        return __builtin_bit_cast(half8_t, d);
     };
 
-    const int xq = tid % TX;
-    // x-pass mapping: consecutive lanes take consecutive rows of one segment
-    // (bank-conflict free with the padded pitch).  Row slots are padded to a
-    // multiple of 8; surplus lanes redo the last row (no divergent branch) and
-    // store to the spare row LY.
-    const int xrow = min(tid % S::XR, S::LY - 1);
-    const int xroww = (tid % S::XR < S::LY) ? xrow : S::LY;
-    const int xseg = min(tid / S::XR, S::NSEG - 1);
-    auto half = [](uint32_t w, int h) -> uint32_t {
-        return h ? (w >> (8 * sizeof(T))) : (w & ((1u << (8 * sizeof(T))) - 1u));
-    };
-    // x-pass, part 1: this thread's raw row segment, read from LDS at the top
-    // of the iteration so the reads overlap the y-pass
-    uint32_t xw[S::SWW];
-    auto xload = [&](int slot) {
-        const uint32_t* rp = sm.raw[slot] + xrow * LX + xseg * (S::SEG / EPW);
+    constexpr float kP = -1152.f * (2 * R + 1), kQ = SPLIT ? kP : 2.f * kP;
+    const f32x4_t cp = {kP, kP, kP, kP}, cq = {kQ, kQ, kQ, kQ}, zero = {0.f, 0.f, 0.f, 0.f};
+
+    // ---- outputs as stored: whole words, 4 columns per thread and TXW / 4
+    // adjacent threads to a row; or voxels, TXW threads to a row.  Outputs
+    // outside the volume get the plane size as their offset, and slices that
+    // are not the strip's an empty buffer resource: either is dropped by the
+    // range check, so every iteration issues the same memory operations and
+    // its waits can leave the younger ones in flight.
+    constexpr int kPer = WORDS ? 4 : 1, kRows = kT * kPer / TXW, kStores = TY / kRows;
+    const int sc = kPer * (tid % (TXW / kPer)), srow = tid / (TXW / kPer);
+    const uint32_t sbase = ((uint32_t)(y0 + srow) * (uint32_t)nx + (uint32_t)(x0 + sc)) * (uint32_t)sizeof(T);
+    const uint32_t sstep = (uint32_t)(kRows * nx) * (uint32_t)sizeof(T);
+    const int srows = x0 + sc < nx ? ny - y0 - srow : 0;  // rows from srow on inside the volume
+    T* wp = out + (size_t)z0 * plane;
+    auto store_out = [&](int zo, int buf) {
+        const bool live = zo >= z0 && zo < z1;
+        const rsrc_t wr = make_rsrc(wp, live ? pbytes : 0u);
+        wp += live ? plane : 0;
 #pragma unroll
-        for (int i = 0; i < S::SWW; i += 4) {
-            if (i + 4 <= S::SWW) {
-                const uint4 t4 = *reinterpret_cast<const uint4*>(rp + i);
-                xw[i] = t4.x;
-                xw[i + 1] = t4.y;
-                xw[i + 2] = t4.z;
-                xw[i + 3] = t4.w;
+        for (int i = 0; i < kStores; ++i) {
+            const T* p = &sm.outs[buf][srow + i * kRows][sc];
+            int rows = srows;
+            if constexpr (kStores > 2) asm volatile("" : "+v"(rows));  // eight offsets kept would spill
+            const uint32_t so = i * kRows < rows ? sbase + (uint32_t)i * sstep : pbytes;
+            if constexpr (!WORDS) {
+                // rows that start anywhere share cache lines with the tiles
+                // beside them: kept in L2 until those are whole (64 x 16
+                // tiles, 511 x 512 x 512 uint16, r = 3: 245 -> 200 us)
+                buffer_store<T, 0>(*p, wr, so, 0u);
+            } else if constexpr (sizeof(T) == 2) {
+                using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
+                __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(p), wr, so, 0, kStoreNT);
             } else {
-                const uint2 t2 = *reinterpret_cast<const uint2*>(rp + i);
-                xw[i] = t2.x;
-                xw[i + 1] = t2.y;
+                __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t*>(p), wr, so, 0, kStoreNT);
             }
         }
     };
-    // OR of every qx this thread formed (kM9Packed: must stay below 2^16)
-    uint32_t qor = 0;
-    // x-pass, part 2: prefix sums over the segment, results written to LDS;
-    // el(i) is raw element i of the segment
-    auto xsums = [&](int buf, auto el) {
-        uint32_t pp[S::SEG], qq[S::SEG], c[S::SW];
-        c[0] = el(0);
-#pragma unroll
-        for (int i = 1; i < S::SW; ++i) c[i] = c[i - 1] + el(i);
-#pragma unroll
-        for (int m = 0; m < S::SEG; ++m) {
-            if constexpr (!kBox) qq[m] = c[m + 4 * R] - (m ? c[m - 1] : 0u) + el(m + 2 * R);
-            pp[m] = c[m + 3 * R] - c[m + R - 1];
-        }
-        if constexpr (kPQ) {
-#pragma unroll
-            for (int m = 0; m < S::SEG; ++m) {
-                if constexpr (kCheck) qor |= qq[m];
-                pp[m] |= qq[m] << 16;
-            }
-        }
-        uint32_t* pd = sm.px[buf] + xroww * PXP + xseg * S::SEG;
-#pragma unroll
-        for (int m = 0; m < S::SEG; m += 4) {
-            *reinterpret_cast<uint4*>(pd + m) = make_uint4(pp[m], pp[m + 1], pp[m + 2], pp[m + 3]);
-            if constexpr (MODE == kM9Exact) {
-                uint32_t* qd = sm.qx[buf] + xroww * PXP + xseg * S::SEG;
-                *reinterpret_cast<uint4*>(qd + m) =
-                    make_uint4(qq[m], qq[m + 1], qq[m + 2], qq[m + 3]);
-            }
-        }
-    };
-    auto xpass = [&](int buf) {
-        if constexpr (PK) {
-            xsums(buf, [&](int i) -> uint32_t { return half(xw[i / 2], i & 1); });
-        } else {
-            xsums(buf, [&](int i) -> uint32_t { return xw[i]; });
-        }
-    };
 
-    // y-pass / ring ownership: column xq, rows yg*YO .. yg*YO+YO-1
-    const int yg = tid / TX;
-    const int xo = x0 + xq, ybase = y0 + yg * YO;
-    const uint32_t voff = (uint32_t)((size_t)ybase * g.nx + xo) * (uint32_t)sizeof(T);
-    const uint32_t rowb = (uint32_t)g.nx * (uint32_t)sizeof(T);
-    // per-row store offsets; rows or columns outside the volume get the plane
-    // size, which the range check of the store's buffer resource drops
-    uint32_t soff[YO];
+    // rings: Q and V hold r slices, G 2r+1 (P of the mean filter in G)
+    Z qr[D][NO][4], vr[D][NO][4], gr[D][NO][4], acc[NO][4];
 #pragma unroll
-    for (int m = 0; m < YO; ++m)
-        soff[m] = (xo < g.nx && ybase + m < g.ny) ? voff + (uint32_t)m * rowb : pbytes;
+    for (int o = 0; o < NO; ++o)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            acc[o][i] = 0;
+#pragma unroll
+            for (int u = 0; u < D; ++u) qr[u][o][i] = vr[u][o][i] = gr[u][o][i] = 0;
+        }
 
-    // ring slots of P, Q and G (slice s in slot s mod D) and the running sum
-    uint32_t pr[D][YO], qr[D][YO], gr[D][YO], acc[YO];
-#pragma unroll
-    for (int m = 0; m < YO; ++m) {
-        acc[m] = 0;
-#pragma unroll
-        for (int u = 0; u < D; ++u) pr[u][m] = qr[u][m] = gr[u][m] = 0;
-    }
-
-    // The y-pass of the first iteration reads x-pass buffer 1 before any
-    // x-pass wrote it: zeros there give zero plane sums.  The staging and the
-    // passes run in every iteration (the extra ones at the end read clamped
-    // slices and their results are never stored), so the unrolled block is
-    // one basic block the compiler can interleave.
-    for (int i = tid; i < S::LY * PXP; i += S::THREADS) {
-        sm.px[1][i] = 0;
-        if constexpr (MODE == kM9Exact) sm.qx[1][i] = 0;
-    }
-    if constexpr (kCheck) {
-        if (tid == 0) sm.flag = 0;
-    }
-    const int ns = (z1 - z0) + 2 * H;  // input slices z0-2r .. z1-1+2r
-    // the YO stores of output slice zo; zo < 0 stores to an empty buffer
-    // resource (every access dropped), so each call issues exactly YO stores
-    auto store_out = [&](int zo, const uint32_t(&o)[YO]) {
-        const rsrc_t wr = make_rsrc(out + (size_t)max(zo, 0) * plane, zo >= 0 ? pbytes : 0u);
-#pragma unroll
-        for (int m = 0; m < YO; ++m) buffer_store<T>(o[m], wr, soff[m], 0u);
-    };
-    // prologue: slices 0 .. PF-1, each but the first preceded by YO (dropped)
-    // stores so the operation pattern matches the loop's
-    stage(z0 - H, 0);
+    const int ns = (z1 - z0) + LAG;  // input slices z0 - ZH .. z1 - 1 + ZH
+    // vector-memory operations younger than a slice's staging when it is waited for
+    constexpr int kWait = (PF - 1) * (NLOAD + kStores);
+    // each slice but the first after dropped stores: the operations of an iteration
+    stage(0);
 #pragma unroll
     for (int p = 1; p < PF; ++p) {
-        store_out(-1, acc);
-        stage(z0 - H + p, p);
+        store_out(-1, 0);
+        stage(p);
     }
-    wait_vmem_le<S::VMWAIT>();
+    wait_vmem_le<kWait>();
     barrier_lds();
-    int zdone = z1;
-    // iteration k: x-pass of slice k, y-pass of slice k-1 and its outputs;
-    // whole blocks of D iterations (no exit inside the unrolled block)
-    for (int kb = 0; kb <= ns; kb += D) {
+    half4_t d1[DIG][NQ][NR];  // x-pass of the previous iteration's slice
+#pragma unroll
+    for (int t = 0; t < DIG; ++t)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int rt = 0; rt < NR; ++rt) d1[t][q][rt] = half4_t{0, 0, 0, 0};
+    // whole blocks of D slices (no exit inside the unrolled block); the slices
+    // past the end are clamped and store nothing
+    for (int kb = 0; kb <= ns + 1; kb += D) {
 #pragma unroll
         for (int u = 0; u < D; ++u) {
             const int k = kb + u;
-            xload(u % NRB);  // slice k, staged PF iterations ago (k mod NRB)
+            const int us = (u + D - 1) % D;  // ring slot of slice k-1
             const int buf = u & 1;  // == k & 1 because D is even
-            const int pb = buf ^ 1;
-            uint32_t pv[S::NPV], qv[S::NQV];
-            if constexpr (kPQ) {
-                // one word per row: px in the low half, qx in the high half;
-                // the px rows yg*YO+R .. are rows R .. of the qx range
-                uint32_t wv[S::NQV];
+            // outputs of iteration k-1
+            const int zo = z0 + k - 2 - LAG;
+            store_out(zo, buf ^ 1);
+            stage((u + PF) % NRB);  // slice k+PF; the buffer held slice k-1
 #pragma unroll
-                for (int i = 0; i < S::NQV; ++i) wv[i] = sm.px[pb][(yg * YO + i) * PXP + xq];
+            for (int o = 0; o < NO; ++o) {
+                auto col = [&](int t, int q) {
+                    return __builtin_shufflevector(d1[t][q][o], d1[t][q][o + 1], 0, 1, 2, 3, 4, 5, 6, 7);
+                };
+                f32x4_t sp = zero, sq = zero;
 #pragma unroll
-                for (int i = 0; i < S::NQV; ++i) qv[i] = wv[i] >> 16;
-#pragma unroll
-                for (int i = 0; i < S::NPV; ++i) pv[i] = wv[i + R] & 0xffffu;
-            } else {
-#pragma unroll
-                for (int i = 0; i < S::NPV; ++i) pv[i] = sm.px[pb][(yg * YO + R + i) * PXP + xq];
-                if constexpr (MODE == kM9Exact) {
-#pragma unroll
-                    for (int i = 0; i < S::NQV; ++i) qv[i] = sm.qx[pb][(yg * YO + i) * PXP + xq];
-                }
-            }
-            {
-                // y-pass of slice s = k-1 into ring slot us; slot (us+1) mod D
-                // holds slice s-2r-1, the one that leaves the running sum
-                const int us = (u + D - 1) % D;
-                uint32_t cp[S::NPV], o[YO];
-                cp[0] = pv[0];
-#pragma unroll
-                for (int i = 1; i < S::NPV; ++i) cp[i] = cp[i - 1] + pv[i];
-#pragma unroll
-                for (int m = 0; m < YO; ++m) pr[us][m] = cp[m + 2 * R] - (m ? cp[m - 1] : 0u);
-                if constexpr (kBox) {
-#pragma unroll
-                    for (int m = 0; m < YO; ++m) {
-                        acc[m] += pr[us][m] - pr[(us + 1) % D][m];
-                        o[m] = round_div_odd(acc[m], inv_div);
+                for (int t = 0; t < DIG; ++t) {
+                    sp = __builtin_amdgcn_mfma_f32_16x16x32_f16(col(t, 0), wyp[t], sp, 0, 0, 0);
+                    if constexpr (!BOX) {
+                        sq = __builtin_amdgcn_mfma_f32_16x16x32_f16(col(t, 1), wyq[t], sq, 0, 0, 0);
+                        if constexpr (SPLIT)
+                            sq = __builtin_amdgcn_mfma_f32_16x16x32_f16(col(t, NQ - 1), wyq[t], sq, 0, 0, 0);
                     }
+                }
+                uint32_t v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const Z p = FP ? (Z)sp[i] : (Z)(int)sp[i];
+                    Z gn = p;
+                    if constexpr (!BOX) {
+                        const Z q = FP ? (Z)sq[i] : (Z)(int)sq[i];
+                        // slot (u - R) mod D: r slices ago
+                        gn = q + vr[(us + D - R) % D][o][i];
+                        vr[us][o][i] = p + qr[(us + D - R) % D][o][i];
+                        qr[us][o][i] = q;
+                    }
+                    // slot (u + 1) mod D holds G of 2r+1 slices ago
+                    acc[o][i] += gn - gr[(us + 1) % D][o][i];
+                    gr[us][o][i] = gn;
+                    if constexpr (FP) {
+                        // S' = S - 128 * 9n with |S' / 9n| <= 128: the fp32
+                        // product is off by at most 2^-16, less than the
+                        // 1/(18n) >= 7.6e-5 to the nearest half
+                        const float t = __builtin_fmaf((float)acc[o][i], (float)inv_div, 12582912.f + kBias);
+                        v[i] = __builtin_bit_cast(uint32_t, t) - 0x4B400000u;
+                    } else {
+                        // as round_div_odd, with the bias put back
+                        const double t = __builtin_fma((double)(int)acc[o][i], inv_div, 4503599627370496.0 + (double)kBias);
+                        v[i] = (uint32_t)__builtin_bit_cast(uint64_t, t);
+                    }
+                    if (GATE && v[i] < gate) v[i] = 0;
+                }
+                // row l of the block, columns 16 wave + 4 gq ..
+                using out_t = uint32_t __attribute__((ext_vector_type(sizeof(T))));
+                out_t w;
+                if constexpr (sizeof(T) == 2) {
+                    w[0] = v[0] | (v[1] << 16);
+                    w[1] = v[2] | (v[3] << 16);
                 } else {
-                    uint32_t cq[S::NQV];
-                    cq[0] = qv[0];
+                    w[0] = v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24);
+                }
+                *reinterpret_cast<out_t*>(&sm.outs[buf][16 * o + l][16 * wave + 4 * gq]) = w;
+            }
+            // x-pass of every raw block, rounded to f16 (exact)
 #pragma unroll
-                    for (int i = 1; i < S::NQV; ++i) cq[i] = cq[i - 1] + qv[i];
+            for (int rt = 0; rt < NR; ++rt) {
+                const words_t w = read_raw(u % NRB, rt);
 #pragma unroll
-                    for (int m = 0; m < YO; ++m) {
-                        qr[us][m] = cq[m + 4 * R] - (m ? cq[m - 1] : 0u) + qv[m + 2 * R];
-                        gr[us][m] = pr[(us + D - R) % D][m] + qr[us][m] + qr[(us + 2) % D][m];
-                        acc[m] += gr[us][m] - gr[(us + 1) % D][m];
-                        o[m] = round_div_odd(acc[m], inv_div);
+                for (int t = 0; t < DIG; ++t) {
+                    const half8_t a = operand(w, t);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        const f32x4_t s = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            a, wx[q], q ? cq : cp, 0, 0, 0);
+                        const auto lo = __builtin_amdgcn_cvt_pkrtz(s[0], s[1]);
+                        const auto hi = __builtin_amdgcn_cvt_pkrtz(s[2], s[3]);
+                        d1[t][q][rt] = half4_t{(_Float16)lo[0], (_Float16)lo[1], (_Float16)hi[0], (_Float16)hi[1]};
                     }
                 }
-#pragma unroll
-                for (int m = 0; m < YO; ++m)
-                    if (GATE && o[m] < gate) o[m] = 0;
-                const int zo = z0 + k - 1 - LAG;
-                store_out((zo >= z0 && zo < z1) ? zo : -1, o);
             }
-            // slice k+PF takes the buffer slice k-1 used, read in the previous
-            // iteration
-            stage(z0 - H + k + PF, (u + PF) % NRB);
-            xpass(buf);
-            wait_vmem_le<S::VMWAIT>();  // slice k+1 has landed
-            barrier_lds();
-        }
-        if constexpr (kCheck) {
-            // block end: publish any qx >= 2^16 formed so far, then stop the
-            // whole workgroup if some thread saw one.  The previous check
-            // cleared the x-passes of iterations before kb, and the outputs of
-            // iteration k read the x-pass of iteration k-1 only, so outputs of
-            // iterations up to kb are final
-            if (qor >> 16) sm.flag = 1;
-            barrier_lds();
-            if (sm.flag) {
-                zdone = max(z0, z0 + kb - 1 - LAG);
-                break;
+            if constexpr (!WORDS) {
+                rlead = (rlead + ((zr >= 0 && zr < g.nz - 1) ? pbytes : 0u)) & 3u;
+                ++zr;
             }
+            wait_vmem_le<kWait>();  // slice k+1 has landed
+            barrier_lds();
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     // drain the staging of the slices past the end before the LDS is reused
     wait_vmem();
     barrier_lds();
-    return zdone;
 }
 
-// Whether packed mode can stop, so that a kernel needs the unpacked bodies.
-template <typename T, int R, bool BOX>
-constexpr bool m9_needs_exact()
-{
-    return !BOX && m9_packed_may_overflow<T, R>();
-}
-
-// LDS of every body a kernel runs: packed (or box) mode with paired and
-// element-wise staging, and the unpacked fallback where packed mode can stop
-// (where it cannot, those members repeat the packed layouts).
-template <int R, int TY, int TXW, typename T, bool BOX = false>
-union M9SmemAny {
-    static constexpr int kMode = BOX ? kM9Box : kM9Packed;
-    static constexpr int kFallback = m9_needs_exact<T, R, BOX>() ? kM9Exact : kMode;
-    M9Smem<R, TY, TXW, true, kMode> p;
-    M9Smem<R, TY, TXW, false, kMode> e;
-    M9Smem<R, TY, TXW, true, kFallback> px;
-    M9Smem<R, TY, TXW, false, kFallback> ex;
-};
-
-// One tile; `pairs` (mean9_pairs_ok for the volume) selects paired staging
-// for the tiles whose x halo stays inside the volume.  MEAN9 runs packed and,
-// where that can stop, unpacked from the first slice a stopped packed run
-// left unfinished.
-// tid: threadIdx.x (see tile_tid for loops over several tiles).
+// One tile.  words: see WORDS.  tid: threadIdx.x (see tile_tid for loops over
+// several tiles).
 template <int R, int TY, typename T, bool GATE, int TXW = 64, bool BOX = false>
-__device__ __forceinline__ void mean9_tile(M9SmemAny<R, TY, TXW, T, BOX>& sm, bool pairs,
+__device__ __forceinline__ void mean9_tile(M9Smem<R, TY, TXW, T>& sm, bool words,
                                            const T* __restrict__ in, T* __restrict__ out, Geom g,
                                            int x0, int y0, int z0, int z1, uint32_t gate,
                                            double inv_div, int tid)
 {
-    constexpr int H = 2 * R, LXE = TXW + 4 * R;
-    constexpr int kMode = BOX ? kM9Box : kM9Packed;
-    if (pairs && x0 - H >= 0 && x0 - H + LXE <= g.nx) {
-        const int zr = mean9_tile_body<R, TY, T, GATE, TXW, true, kMode>(
-            sm.p, in, out, g, x0, y0, z0, z1, gate, inv_div, tid);
-        if constexpr (m9_needs_exact<T, R, BOX>())
-            if (zr < z1)
-                mean9_tile_body<R, TY, T, GATE, TXW, true, kM9Exact>(sm.px, in, out, g, x0, y0, zr,
-                                                                     z1, gate, inv_div, tid);
-    } else {
-        const int zr = mean9_tile_body<R, TY, T, GATE, TXW, false, kMode>(
-            sm.e, in, out, g, x0, y0, z0, z1, gate, inv_div, tid);
-        if constexpr (m9_needs_exact<T, R, BOX>())
-            if (zr < z1)
-                mean9_tile_body<R, TY, T, GATE, TXW, false, kM9Exact>(sm.ex, in, out, g, x0, y0,
-                                                                      zr, z1, gate, inv_div, tid);
-    }
+    if (words)
+        mean9_body<R, TY, T, GATE, TXW, BOX, true>(sm, in, out, g, x0, y0, z0, z1, gate, inv_div, tid);
+    else
+        mean9_body<R, TY, T, GATE, TXW, BOX, false>(sm, in, out, g, x0, y0, z0, z1, gate, inv_div, tid);
 }
 
 }  // namespace lnf

@@ -1,0 +1,86 @@
+"""MEAN9 and the mean filter on the matrix-core tiles, at the sizes where they
+can go wrong: rows of every alignment (nx mod 4, and volumes that start at
+every byte of a word), volumes narrower and lower than a block of 16 and a
+window of 32, one more and one less than a tile, both faces in one window, and
+values whose digits reach both ends of their range.  Integer work: every byte
+equals the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import compare as ocmp
+from paper_1807_03119_amd import _lib
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DTYPES = {"u8": (torch.uint8, np.uint8), "u16": (torch.uint16, np.uint16)}
+# nx around 8, 16, 32, 64, 128 and 144 with every remainder mod 4; ny around 16 and 32
+DIMS = [(1, 1, 3), (5, 2, 4), (7, 17, 3), (8, 15, 9), (15, 33, 5), (16, 16, 16), (17, 31, 6),
+        (30, 9, 11), (33, 32, 5), (63, 18, 4), (64, 47, 3), (66, 16, 7), (127, 34, 3),
+        (128, 33, 4), (131, 20, 5), (145, 49, 3), (270, 17, 2)]
+
+
+def _values(dims, dtype, kind, seed):
+    nx, ny, nz = dims
+    rng = np.random.default_rng(seed)
+    top = np.iinfo(dtype).max
+    if kind == "uniform":
+        return rng.integers(0, top + 1, (nz, ny, nx)).astype(dtype)
+    if kind == "max":
+        return np.full((nz, ny, nx), top, dtype)
+    # only bytes 0x00, 0x7f, 0x80 and 0xff: the extremes of each biased digit
+    b = np.array([0x00, 0x7F, 0x80, 0xFF])
+    v = b[rng.integers(0, 4, (nz, ny, nx))]
+    if dtype == np.uint16:
+        v = v + 256 * b[rng.integers(0, 4, (nz, ny, nx))]
+    return v.astype(dtype)
+
+
+def _at_offset(vol, torch_dtype, lead):
+    """The volume on the device, starting `lead` elements into an allocation."""
+    n = vol.size
+    buf = torch.zeros(n + lead + 64, dtype=torch_dtype, device="cuda")
+    t = buf[lead:lead + n].view(vol.shape)
+    t.copy_(torch.from_numpy(vol).cuda())
+    return t
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+@pytest.mark.parametrize("dt", ["u8", "u16"])
+def test_tile_edges_every_variant_and_alignment(dt, r):
+    from paper_1807_03119_amd.api import Filter
+    tdt, ndt = DTYPES[dt]
+    code = _lib.LNF_U8 if dt == "u8" else _lib.LNF_U16
+    f = Filter(_lib.LNF_MEAN9, 0)
+    kinds = ["uniform", "digits", "max"]
+    for i, dims in enumerate(DIMS):
+        vol = _values(dims, ndt, kinds[i % 3], 7000 + i)
+        want = oracle.filter_volume(vol, r)
+        want_mean = ocmp.mean_filter(vol, r)
+        for lead in range(4 // ndt().itemsize):
+            dev = _at_offset(vol, tdt, lead)
+            out = _at_offset(np.zeros_like(vol), tdt, (lead + i) % 3)
+            for variant in range(-1, _lib.lnf_tile_variants(_lib.LNF_MEAN9, code, r)):
+                for zs in (0, 3):
+                    got = f(dev, r, out=out, variant=variant, zs=zs).cpu().numpy()
+                    assert np.array_equal(got, want), (dims, lead, variant, zs)
+            got = f.mean(dev, r, out=out).cpu().numpy()
+            assert np.array_equal(got, want_mean), (dims, lead, "mean")
+    f.close()
+
+
+def test_stores_stay_inside_the_volume():
+    """No byte before or after an output of odd rows changes."""
+    from paper_1807_03119_amd.api import Filter
+    f = Filter(_lib.LNF_MEAN9, 0)
+    for nx, ny, nz in ((67, 19, 5), (68, 33, 4), (3, 2, 2)):
+        vol = torch.full((nz, ny, nx), 500, dtype=torch.uint16, device="cuda")
+        buf = torch.full((nx * ny * nz + 512,), 7, dtype=torch.uint16, device="cuda")
+        for lead in (255, 256):
+            f(vol, 3, out=buf[lead:lead + vol.numel()].view(vol.shape))
+            host = buf.cpu().numpy()
+            assert (host[:lead] == 7).all() and (host[lead + vol.numel():] == 7).all()
+            assert (host[lead:lead + vol.numel()] == 500).all()
+            buf.view(torch.int16).fill_(7)
+    f.close()
