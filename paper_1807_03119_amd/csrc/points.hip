@@ -3,15 +3,25 @@
 // inside the renderer (Section "Our Method"; Results, Performance), so the
 // work is a sparse gather rather than a dense stencil.
 //
-// One 64-lane wavefront per point.  The nine clusters cover the (4r+1)^3 block
-// around the point (coordinates clamped into the volume); the lanes split its
-// (4r+1)^2 x-rows.  Each row is read once and summed over three x-ranges: left
-// [-2r, 0], right [0, 2r] and centre [-r, r].  A row at (dy, dz) then belongs to
-// the corner clusters whose y- and z-ranges hold it (left or right part by the
-// cluster's x side) and, when |dy|, |dz| <= r, to the centre cluster.  Per-lane
-// cluster sums (and sums of squares for MINVAR9) are combined with butterfly
-// wavefront reductions (cross-lane shuffles); MEAN9 needs only their total.
-// Lane 0 applies the rule, rounding and gate.
+// Sixteen lanes per point, four neighbouring points of the list per wavefront
+// (lane % 4, so that points beside each other, which share most of their rows,
+// read the same cache lines in one instruction).  The nine clusters cover the
+// (4r+1)^3 block around the point (coordinates clamped into the volume); the
+// sixteen lanes split its (4r+1)^2 x-rows.  A row is read as the r * sizeof(T)
+// + 1 aligned words that hold its 4r+1 voxels, for every alignment, and
+// shifted into place; rows that leave the volume in x are read voxel by voxel.
+// MEAN9 needs two weighted sums of a row, S = sum_rows c(dy) c(dz) sum_x c(dx) v
+// + sum_{|dy|,|dz| <= r} sum_{|dx| <= r} v with c = 1, and 2 at 0: integer dot
+// products of the packed words with constant weights.  MINVAR9 sums each row
+// (and its squares) over the left, right and centre ranges of the clusters,
+// which go to the corner clusters whose y- and z-ranges hold the row and, when
+// |dy|, |dz| <= r, to the centre cluster.  The lanes' sums are combined with
+// cross-lane shuffles; one lane applies the rule, rounding and gate.
+//
+// What bounds it: the rows' cache-line requests (169 rows a point at r = 3).
+// One wavefront per point with 13 two-byte loads a row took 925 us for the
+// 262144 rays of a 512^3 uint16 volume (r = 3, MEAN9); this takes 179 (MINVAR9
+// 969 and 222).  Scattered points are bound by their cache misses (995 -> 905).
 //
 // The first-hit pass produces that point list for rays parallel to z: per
 // pixel (x, y), the first voxel of the column, in the ray's direction, whose
@@ -24,6 +34,8 @@
 // columns up to their hits.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "lnf.h"
 #include "lnf_ctx.h"
@@ -32,100 +44,153 @@
 namespace lnf {
 namespace {
 
-constexpr int kWaves = 4;  // points per workgroup
+constexpr int kPointLanes = 16;                 // lanes per point
+constexpr int kPointThreads = 256;
+constexpr int kGroupPoints = kPointThreads / kPointLanes;
 
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
+// Sum over the sixteen lanes of a point (lane bits 2 to 5).
+template <typename V>
+__device__ __forceinline__ V point_sum(V v)
 {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
     return v;
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v)
+// The weights of word a of a row's packed voxels: MEAN9's c(dx) (BOX: 1 for
+// |dx| <= r), 0 past the row.
+template <int R, typename T, bool BOX>
+constexpr uint32_t row_weights(int a)
 {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    constexpr int kPer = 4 / (int)sizeof(T);
+    uint32_t w = 0;
+    for (int b = 0; b < kPer; ++b) {
+        const int dx = a * kPer + b - 2 * R;
+        uint32_t c = dx > 2 * R ? 0u : dx == 0 ? 2u : 1u;
+        if (BOX) c = dx >= -R && dx <= R ? 1u : 0u;
+        w |= c << (8 * (int)sizeof(T) * b);
+    }
+    return w;
 }
 
 template <int R, typename T, int RULE>
-__global__ __launch_bounds__(64 * kWaves) void filter_points_kernel(const T* __restrict__ in,
-                                                                     Geom g, const int32_t* xyz,
-                                                                     int64_t n, uint32_t gate,
-                                                                     uint32_t* out)
+__global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
+    const T* __restrict__ in, Geom g, const int32_t* __restrict__ xyz, int64_t n, uint32_t gate,
+    uint32_t* __restrict__ out)
 {
     constexpr int M = 2 * R + 1, NB = M * M * M;
     constexpr int W = 4 * R + 1, NROW = W * W;  // side and x-rows of the nine clusters' block
+    constexpr int ND = R * (int)sizeof(T) + 1;  // aligned words that hold a row
+    constexpr int kPer = 4 / (int)sizeof(T);
     constexpr bool VAR = RULE == LNF_MINVAR9;
-    const int lane = threadIdx.x & 63;
-    const int64_t p = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-    if (p >= n) return;  // whole wavefront exits together
-    // the point is the same for the whole wavefront: keep it scalar
-    const int px = __builtin_amdgcn_readfirstlane(xyz[3 * p]);
-    const int py = __builtin_amdgcn_readfirstlane(xyz[3 * p + 1]);
-    const int pz = __builtin_amdgcn_readfirstlane(xyz[3 * p + 2]);
-    if (px < 0 || py < 0 || pz < 0 || px >= g.nx || py >= g.ny || pz >= g.nz) {
-        if (lane == 0) out[p] = 0xffffffffu;  // point outside the volume
-        return;
-    }
+    // squares: uint32 holds a cluster's for uint8 (729 * 255^2), fp64 for uint16
+    using Q = std::conditional_t<sizeof(T) == 1, uint32_t, double>;
+    const int lane = threadIdx.x & 63, sub = lane >> 2;
+    const int64_t pi = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kGroupPoints +
+                       (threadIdx.x >> 6) * 4 + (lane & 3);
+    const int64_t p = pi < n ? pi : n - 1;  // lanes past the list redo its last point
+    int px = xyz[3 * p], py = xyz[3 * p + 1], pz = xyz[3 * p + 2];
+    const bool inside = px >= 0 && py >= 0 && pz >= 0 && px < g.nx && py < g.ny && pz < g.nz;
+    if (!inside) px = py = pz = 0;
     const size_t nx = g.nx, plane = (size_t)g.nx * g.ny;
-    int xs[W];  // clamped x of the row's samples (the same for every row)
-#pragma unroll
-    for (int i = 0; i < W; ++i) xs[i] = clampi(px - 2 * R + i, 0, g.nx - 1);
+    const bool whole = px >= 2 * R && px + 2 * R < g.nx;  // rows inside the volume in x
+
     uint32_t s[9];
-    double q[9];
+    Q q[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
         s[k] = 0;
-        q[k] = 0.0;
+        q[k] = 0;
     }
-    for (int row = lane; row < NROW; row += 64) {
-        const int dy = row % W - 2 * R, dz = row / W - 2 * R;
+    int dy = sub % W - 2 * R, dz = sub / W - 2 * R;
+    // points outside the volume read nothing
+    for (int row = inside ? sub : NROW; row < NROW; row += kPointLanes) {
         const int y = clampi(py + dy, 0, g.ny - 1), z = clampi(pz + dz, 0, g.nz - 1);
         const T* rp = in + (size_t)z * plane + (size_t)y * nx;
-        uint32_t v[W];
+        uint32_t w[ND];  // packed voxels from px - 2R on
+        if (whole) {
+            const uintptr_t at = reinterpret_cast<uintptr_t>(rp + (px - 2 * R));
+            const uint32_t* wp = reinterpret_cast<const uint32_t*>(at & ~(uintptr_t)3);
 #pragma unroll
-        for (int i = 0; i < W; ++i) v[i] = rp[xs[i]];
-        uint32_t left = 0, right = 0, centre = 0;
-        double ql = 0.0, qr = 0.0, qc = 0.0;
+            for (int a = 0; a < ND; ++a) w[a] = wp[a];
 #pragma unroll
-        for (int i = 0; i < W; ++i) {
-            if (i <= 2 * R) left += v[i];
-            if (i >= 2 * R) right += v[i];
-            if (i >= R && i <= 3 * R) centre += v[i];
-            if constexpr (VAR) {
-                const double vv = (double)v[i] * (double)v[i];  // exact below 2^32
-                if (i <= 2 * R) ql += vv;
-                if (i >= 2 * R) qr += vv;
-                if (i >= R && i <= 3 * R) qc += vv;
+            for (int a = 0; a < ND; ++a)
+                w[a] = __builtin_amdgcn_alignbyte(a + 1 < ND ? w[a + 1] : 0u, w[a], (uint32_t)at);
+        } else {
+#pragma unroll
+            for (int a = 0; a < ND; ++a) {
+                w[a] = 0;
+#pragma unroll
+                for (int b = 0; b < kPer; ++b)
+                    if (a * kPer + b < W)
+                        w[a] |= (uint32_t)rp[clampi(px - 2 * R + a * kPer + b, 0, g.nx - 1)]
+                                << (8 * (int)sizeof(T) * b);
             }
         }
         const bool inc = dy >= -R && dy <= R && dz >= -R && dz <= R;
-        s[0] += inc ? centre : 0u;
-        if constexpr (VAR) q[0] += inc ? qc : 0.0;
+        if constexpr (!VAR) {
+            uint32_t c = 0, box = 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {  // cluster j + 1: x, y, z side by bits 0, 1, 2
-            const bool in_yz = ((j & 2) ? dy >= 0 : dy <= 0) && ((j & 4) ? dz >= 0 : dz <= 0);
-            s[j + 1] += in_yz ? ((j & 1) ? right : left) : 0u;
-            if constexpr (VAR) q[j + 1] += in_yz ? ((j & 1) ? qr : ql) : 0.0;
+            for (int a = 0; a < ND; ++a) {
+                if constexpr (sizeof(T) == 2) {
+                    using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
+                    const u16x2 v = __builtin_bit_cast(u16x2, w[a]);
+                    c = __builtin_amdgcn_udot2(v, __builtin_bit_cast(u16x2, row_weights<R, T, false>(a)), c, false);
+                    box = __builtin_amdgcn_udot2(v, __builtin_bit_cast(u16x2, row_weights<R, T, true>(a)), box, false);
+                } else {
+                    c = __builtin_amdgcn_udot4(w[a], row_weights<R, T, false>(a), c, false);
+                    box = __builtin_amdgcn_udot4(w[a], row_weights<R, T, true>(a), box, false);
+                }
+            }
+            s[0] += (c << ((dy == 0) + (dz == 0))) + (inc ? box : 0u);
+        } else {
+            // sums over [0, R), [R, 2R), 2R, (2R, 3R], (3R, 4R]: the three
+            // ranges are made of them
+            uint32_t t[5] = {0, 0, 0, 0, 0};
+            Q u[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                const uint32_t v = (w[i / kPer] >> (8 * (int)sizeof(T) * (i % kPer))) &
+                                   ((1u << (8 * (int)sizeof(T))) - 1u);
+                const int k = i < R ? 0 : i < 2 * R ? 1 : i == 2 * R ? 2 : i <= 3 * R ? 3 : 4;
+                t[k] += v;
+                u[k] += (Q)(v * v);  // exact: below 2^32
+            }
+            const uint32_t centre = t[1] + t[2] + t[3];
+            const Q qc = u[1] + u[2] + u[3];
+            const uint32_t side[2] = {t[0] + t[1] + t[2], t[2] + t[3] + t[4]};
+            const Q qside[2] = {u[0] + u[1] + u[2], u[2] + u[3] + u[4]};
+            s[0] += inc ? centre : 0u;
+            q[0] += inc ? qc : (Q)0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {  // cluster j + 1: x, y, z side by bits 0, 1, 2
+                const bool in_yz = ((j & 2) ? dy >= 0 : dy <= 0) && ((j & 4) ? dz >= 0 : dz <= 0);
+                s[j + 1] += in_yz ? side[j & 1] : 0u;
+                q[j + 1] += in_yz ? qside[j & 1] : (Q)0;
+            }
+        }
+        // the row kPointLanes further on
+        dy += kPointLanes % W;
+        dz += kPointLanes / W;
+        if (dy > 2 * R) {
+            dy -= W;
+            dz += 1;
         }
     }
     uint32_t o;
     if constexpr (!VAR) {
-        uint32_t total = 0;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) total += s[k];
-        total = wave_sum_u32(total);
-        o = round_div_odd(total, 1.0 / (9.0 * NB));
+        o = round_div_odd(point_sum(s[0]), 1.0 / (9.0 * NB));
     } else {
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            s[k] = wave_sum_u32(s[k]);
-            q[k] = wave_sum_f64(q[k]);
+            s[k] = point_sum(s[k]);
+            q[k] = point_sum(q[k]);
         }
         uint32_t best_s = s[0];
-        double best_v = __builtin_fma((double)NB, q[0], -(double)s[0] * (double)s[0]);
+        double best_v = __builtin_fma((double)NB, (double)q[0], -(double)s[0] * (double)s[0]);
 #pragma unroll
         for (int k = 1; k < 9; ++k) {
-            const double v = __builtin_fma((double)NB, q[k], -(double)s[k] * (double)s[k]);
+            const double v = __builtin_fma((double)NB, (double)q[k], -(double)s[k] * (double)s[k]);
             if (v < best_v) {
                 best_v = v;
                 best_s = s[k];
@@ -133,12 +198,13 @@ __global__ __launch_bounds__(64 * kWaves) void filter_points_kernel(const T* __r
         }
         o = round_div_odd(best_s, 1.0 / NB);
     }
-    if (lane != 0) return;
+    if (sub != 0 || pi >= n) return;
     if (o < gate) o = 0;
-    out[p] = o;
+    out[p] = inside ? o : 0xffffffffu;  // point outside the volume
 }
 
-constexpr int kHitStep = 8;     // slices loaded per step of a ray
+// slices loaded per step of a ray (512^3 uint16, mean depth 49: 43 us with 8, 37 with 16)
+constexpr int kHitStep = 16;
 constexpr int kHitRows = 4;     // wavefronts (pixel rows) per workgroup
 
 template <typename T, bool BACK>
@@ -194,7 +260,7 @@ template <int R, typename T>
 hipError_t launch_points_r(int rule, const void* vol, Geom g, const int32_t* xyz, int64_t n,
                            uint32_t gate, uint32_t* out, hipStream_t s)
 {
-    const dim3 grid((unsigned)((n + kWaves - 1) / kWaves)), block(64 * kWaves);
+    const dim3 grid((unsigned)((n + kGroupPoints - 1) / kGroupPoints)), block(kPointThreads);
     const T* in = static_cast<const T*>(vol);
     if (rule == LNF_MEAN9)
         hipLaunchKernelGGL((filter_points_kernel<R, T, LNF_MEAN9>), grid, block, 0, s, in, g, xyz,

@@ -84,3 +84,32 @@ def test_stores_stay_inside_the_volume():
             assert (host[lead:lead + vol.numel()] == 500).all()
             buf.view(torch.int16).fill_(7)
     f.close()
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+@pytest.mark.parametrize("dt", ["u8", "u16"])
+def test_points_at_faces_and_alignments(dt, r):
+    """Listed points on rows of every alignment: voxels whose rows end at a
+    face, touch it, or leave the volume, points outside it, and lists that do
+    not fill a group of sixteen points."""
+    from paper_1807_03119_amd.api import Filter
+    tdt, ndt = DTYPES[dt]
+    for i, dims in enumerate([(4 * r + 1, 3, 2), (4 * r + 2, 9, 7), (4 * r + 7, 19, 5), (64, 11, 6), (3, 4, 5)]):
+        nx, ny, nz = dims
+        vol = _values(dims, ndt, "digits" if i % 2 else "uniform", 7100 + i)
+        rng = np.random.default_rng(i)
+        pts = [(x, int(rng.integers(0, ny)), int(rng.integers(0, nz))) for x in range(nx)]
+        pts += [(x, y, z) for x in (0, nx - 1) for y in (0, ny - 1) for z in (0, nz - 1)]
+        ok = np.array(pts)
+        out = np.array([(-1, 0, 0), (0, ny, 0), (0, 0, -1), (nx, 0, 0)])
+        for rule, orule in ((_lib.LNF_MEAN9, oracle.MEAN9), (_lib.LNF_MINVAR9, oracle.MINVAR9)):
+            want = np.concatenate([oracle.filter_points(vol, r, ok, orule), np.full(4, 0xFFFFFFFF, np.uint32)])
+            f = Filter(rule, 0)
+            for lead in range(4 // ndt().itemsize):
+                dev = _at_offset(vol, tdt, lead)
+                for n in (len(want), 1, 17):
+                    sel = np.random.default_rng(n).permutation(len(want))[:n]
+                    xyz = torch.from_numpy(np.concatenate([ok, out])[sel].astype(np.int32)).cuda()
+                    got = f.points(dev, r, xyz).cpu().numpy().view(np.uint32)
+                    assert np.array_equal(got, want[sel]), (dims, rule, lead, n)
+            f.close()
