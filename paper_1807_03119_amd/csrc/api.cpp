@@ -152,11 +152,12 @@ TileCfg ctx_tile(const lnf_ctx* h, int rule, int dtype, int radius, Geom g)
 }
 
 hipError_t launch_rule(int rule, uint32_t geom, const void* in, void* out, int dtype, int r,
-                       Geom g, uint32_t gate, TileCfg cfg, hipStream_t s, TileCfg* plan)
+                       Geom g, uint32_t gate, TileCfg cfg, hipStream_t s, TileCfg* plan,
+                       const uint32_t* gate_dev)
 {
-    if (geom) return launch_geometry(rule, geom, in, out, dtype, r, g, gate, cfg.zs, s, plan);
-    if (rule == LNF_MEAN9) return launch_mean9(in, out, dtype, r, g, gate, cfg, s, plan);
-    return launch_minvar9(in, out, dtype, r, g, gate, cfg, s, plan);
+    if (geom) return launch_geometry(rule, geom, in, out, dtype, r, g, gate, cfg.zs, s, plan, gate_dev);
+    if (rule == LNF_MEAN9) return launch_mean9(in, out, dtype, r, g, gate, cfg, s, plan, gate_dev);
+    return launch_minvar9(in, out, dtype, r, g, gate, cfg, s, plan, gate_dev);
 }
 
 TuneKey tune_key(int rule, int dtype, int radius, Geom g)

@@ -404,7 +404,8 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
             Geom g0{0, 0, 0};
             int z = 0, total = tab->c[c].total;
             double dn = gk[c].dn, inv = gk[c].inv;
-            void* args[] = {&dtab, &cls, &nul, &nulo, &g0, &z, &z, &z, &total, &gate, &dn, &inv};
+            const uint32_t* gdev = nullptr;
+            void* args[] = {&dtab, &cls, &nul, &nulo, &g0, &z, &z, &z, &total, &gate, &dn, &inv, &gdev};
             e = hipLaunchKernel(kern[c].fn, dim3(grid[c]), dim3(kern[c].threads), args, 0, stream);
         } else {
             void* args[] = {&dtab, &cls, &gate};

@@ -45,7 +45,7 @@ struct ClassKernel {
 
 // The kernel of a geometry-variant class (cluster.hip): launched with the
 // arguments (table, class, nullptr, nullptr, Geom{}, 0, 0, 0, total, gate, dn,
-// inv) over `total` workgroups; TX x TY output tiles.
+// inv, nullptr) over `total` workgroups; TX x TY output tiles.
 struct GeomClassKernel {
     ClassKernel k;
     int tx, ty;

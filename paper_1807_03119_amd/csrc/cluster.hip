@@ -18,8 +18,10 @@ template <int R, int D, int SHAPE, int RULE, typename T>
 __global__ __launch_bounds__((PTShape<R, D, SHAPE, RULE>::THREADS))
 __attribute__((amdgpu_waves_per_eu(PTShape<R, D, SHAPE, RULE>::WAVES))) void cluster_planes(
     const BatchTable* __restrict__ tab, int cls, const T* __restrict__ in, T* __restrict__ out,
-    Geom g, int zs, int tiles_x, int tiles_y, int total, uint32_t gate, double dn, double inv)
+    Geom g, int zs, int tiles_x, int tiles_y, int total, uint32_t gate, double dn, double inv,
+    const uint32_t* __restrict__ gate_dev)
 {
+    if (gate_dev) gate = *gate_dev;  // a threshold found on the device
     using S = PTShape<R, D, SHAPE, RULE>;
     __shared__ __align__(16) PTSmem<R, D, SHAPE, RULE, T> sm;
     int local = xcd_tile(blockIdx.x, total);
@@ -46,7 +48,7 @@ __attribute__((amdgpu_waves_per_eu(PTShape<R, D, SHAPE, RULE>::WAVES))) void clu
 
 template <int R, int D, int SHAPE, int RULE, typename T>
 hipError_t launch_geom(const void* in, void* out, Geom g, uint32_t gate, int zs, hipStream_t s,
-                       TileCfg* plan)
+                       TileCfg* plan, const uint32_t* gate_dev)
 {
     using S = PTShape<R, D, SHAPE, RULE>;
     const auto kern = cluster_planes<R, D, SHAPE, RULE, T>;
@@ -63,46 +65,46 @@ hipError_t launch_geom(const void* in, void* out, Geom g, uint32_t gate, int zs,
     const double inv = S::VAR ? 1.0 / S::N : 1.0 / (9.0 * S::N);
     hipLaunchKernelGGL(kern, dim3(total), dim3(S::THREADS), 0, s, (const BatchTable*)nullptr, 0,
                        static_cast<const T*>(in), static_cast<T*>(out), g, zs, tiles_x, tiles_y,
-                       total, gate, dn, inv);
+                       total, gate, dn, inv, gate_dev);
     return hipGetLastError();
 }
 
 template <int R, int SHAPE, int RULE, typename T>
 hipError_t launch_offset(int offset, const void* in, void* out, Geom g, uint32_t gate, int zs,
-                         hipStream_t s, TileCfg* plan)
+                         hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
     switch (offset) {
-    case LNF_GEOM_OFFSET_1: return launch_geom<R, 1, SHAPE, RULE, T>(in, out, g, gate, zs, s, plan);
+    case LNF_GEOM_OFFSET_1: return launch_geom<R, 1, SHAPE, RULE, T>(in, out, g, gate, zs, s, plan, gate_dev);
     case LNF_GEOM_OFFSET_2R1:
-        return launch_geom<R, 2 * R + 1, SHAPE, RULE, T>(in, out, g, gate, zs, s, plan);
-    default: return launch_geom<R, R, SHAPE, RULE, T>(in, out, g, gate, zs, s, plan);
+        return launch_geom<R, 2 * R + 1, SHAPE, RULE, T>(in, out, g, gate, zs, s, plan, gate_dev);
+    default: return launch_geom<R, R, SHAPE, RULE, T>(in, out, g, gate, zs, s, plan, gate_dev);
     }
 }
 
 template <int R, typename T>
 hipError_t launch_r(int rule, uint32_t geom, const void* in, void* out, Geom g, uint32_t gate,
-                    int zs, hipStream_t s, TileCfg* plan)
+                    int zs, hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
     const int offset = (int)(geom & (LNF_GEOM_OFFSET_1 | LNF_GEOM_OFFSET_2R1));
     const bool var = rule == LNF_MINVAR9;
     if (geom & LNF_GEOM_CROSS) {
         if (var)
-            return launch_offset<R, kClusterCross, kRuleMinVar9, T>(offset, in, out, g, gate, zs, s, plan);
-        return launch_offset<R, kClusterCross, kRuleMean9, T>(offset, in, out, g, gate, zs, s, plan);
+            return launch_offset<R, kClusterCross, kRuleMinVar9, T>(offset, in, out, g, gate, zs, s, plan, gate_dev);
+        return launch_offset<R, kClusterCross, kRuleMean9, T>(offset, in, out, g, gate, zs, s, plan, gate_dev);
     }
-    if (var) return launch_offset<R, kClusterBox, kRuleMinVar9, T>(offset, in, out, g, gate, zs, s, plan);
-    return launch_offset<R, kClusterBox, kRuleMean9, T>(offset, in, out, g, gate, zs, s, plan);
+    if (var) return launch_offset<R, kClusterBox, kRuleMinVar9, T>(offset, in, out, g, gate, zs, s, plan, gate_dev);
+    return launch_offset<R, kClusterBox, kRuleMean9, T>(offset, in, out, g, gate, zs, s, plan, gate_dev);
 }
 
 template <typename T>
 hipError_t dispatch(int rule, uint32_t geom, int r, const void* in, void* out, Geom g,
-                    uint32_t gate, int zs, hipStream_t s, TileCfg* plan)
+                    uint32_t gate, int zs, hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
     switch (r) {
-    case 1: return launch_r<1, T>(rule, geom, in, out, g, gate, zs, s, plan);
-    case 2: return launch_r<2, T>(rule, geom, in, out, g, gate, zs, s, plan);
-    case 3: return launch_r<3, T>(rule, geom, in, out, g, gate, zs, s, plan);
-    case 4: return launch_r<4, T>(rule, geom, in, out, g, gate, zs, s, plan);
+    case 1: return launch_r<1, T>(rule, geom, in, out, g, gate, zs, s, plan, gate_dev);
+    case 2: return launch_r<2, T>(rule, geom, in, out, g, gate, zs, s, plan, gate_dev);
+    case 3: return launch_r<3, T>(rule, geom, in, out, g, gate, zs, s, plan, gate_dev);
+    case 4: return launch_r<4, T>(rule, geom, in, out, g, gate, zs, s, plan, gate_dev);
     default: return hipErrorInvalidValue;
     }
 }
@@ -157,10 +159,10 @@ GeomClassKernel geometry_class_kernel(int rule, uint32_t geom, int dtype, int r)
 }
 
 hipError_t launch_geometry(int rule, uint32_t geom, const void* in, void* out, int dtype, int r,
-                           Geom g, uint32_t gate, int zs, hipStream_t s, TileCfg* plan)
+                           Geom g, uint32_t gate, int zs, hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
-    if (dtype == LNF_U8) return dispatch<uint8_t>(rule, geom, r, in, out, g, gate, zs, s, plan);
-    return dispatch<uint16_t>(rule, geom, r, in, out, g, gate, zs, s, plan);
+    if (dtype == LNF_U8) return dispatch<uint8_t>(rule, geom, r, in, out, g, gate, zs, s, plan, gate_dev);
+    return dispatch<uint16_t>(rule, geom, r, in, out, g, gate, zs, s, plan, gate_dev);
 }
 
 }  // namespace lnf

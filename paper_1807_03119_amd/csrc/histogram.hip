@@ -86,6 +86,223 @@ __global__ __launch_bounds__(kThreads16) void hist_u16(const uint16_t* __restric
     }
 }
 
+// ---- Otsu's threshold and 2 sigma of a histogram, on the device -------------
+// One workgroup.  The levels come in chunks of 64, one per lane; wave w takes
+// chunks w, w + 16, ... so that the occupied levels, wherever they lie, are
+// spread over the waves.  Chunk totals are scanned over the workgroup, then
+// each occupied chunk is scanned over its lanes.  Counts and weighted sums are
+// exact in uint64 (a volume on the device has fewer than 2^40 voxels).  The
+// criterion is evaluated in fp64, good to 2^-50, and the thresholds within
+// 2^-40 of its maximum are compared exactly (320-bit products), so the result
+// is the host function's for every histogram.
+constexpr int kSelThreads = 1024, kSelWaves = kSelThreads / 64, kSelChunks = 1024;
+
+struct Split {
+    uint64_t n0, s0;  // class 0 (levels below the threshold): count and weighted sum
+    int t;            // the threshold, -1: none
+};
+
+using u128 = unsigned __int128;
+
+// num[a]/den[a] > num[b]/den[b] with num = (N s0 - n0 S)^2, den = n0 (N - n0)
+__device__ bool split_better(const Split& a, const Split& b, uint64_t N, uint64_t S)
+{
+    auto dist = [&](const Split& x) -> u128 {
+        const u128 p = (u128)N * x.s0, q = (u128)x.n0 * S;
+        return p >= q ? p - q : q - p;
+    };
+    // d^2 * e (d < 2^104, e < 2^80) in five 64-bit limbs
+    auto product = [&](u128 d, u128 e, uint64_t(&out)[5]) {
+        const uint64_t d0 = (uint64_t)d, d1 = (uint64_t)(d >> 64);
+        const u128 p00 = (u128)d0 * d0, p01 = (u128)d0 * d1, p11 = (u128)d1 * d1;
+        uint64_t sq[4];
+        sq[0] = (uint64_t)p00;
+        u128 c = (p00 >> 64) + (u128)(uint64_t)p01 * 2;
+        sq[1] = (uint64_t)c;
+        c = (c >> 64) + (u128)(uint64_t)(p01 >> 64) * 2 + (uint64_t)p11;
+        sq[2] = (uint64_t)c;
+        sq[3] = (uint64_t)((c >> 64) + (p11 >> 64));
+        const uint64_t e0 = (uint64_t)e, e1 = (uint64_t)(e >> 64);
+        uint64_t r[5] = {0, 0, 0, 0, 0};
+        u128 carry = 0;
+        for (int i = 0; i < 4; ++i) {
+            carry += (u128)sq[i] * e0;
+            r[i] = (uint64_t)carry;
+            carry >>= 64;
+        }
+        r[4] = (uint64_t)carry;
+        carry = 0;
+        for (int i = 0; i < 4; ++i) {
+            carry += (u128)sq[i] * e1 + r[i + 1];
+            r[i + 1] = (uint64_t)carry;
+            carry >>= 64;
+        }
+        for (int i = 0; i < 5; ++i) out[i] = r[i];
+    };
+    uint64_t x[5], y[5];
+    product(dist(a), (u128)b.n0 * (N - b.n0), x);
+    product(dist(b), (u128)a.n0 * (N - a.n0), y);
+    for (int i = 4; i >= 0; --i)
+        if (x[i] != y[i]) return x[i] > y[i];
+    return false;
+}
+
+template <typename V>
+__device__ V wave_scan(V v, int lane)  // inclusive
+{
+    for (int off = 1; off < 64; off <<= 1) {
+        const V u = __shfl_up(v, off, 64);
+        if (lane >= off) v += u;
+    }
+    return v;
+}
+
+template <typename V>
+__device__ V wave_total(V v)
+{
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_scalar(
+    const unsigned long long* __restrict__ hist, int levels, int sigma, uint32_t* dev,
+    uint32_t* host)
+{
+    __shared__ uint64_t cn[kSelChunks], cs[kSelChunks];  // chunk totals, then what precedes them
+    __shared__ double cmax[kSelChunks];                  // best criterion of a chunk
+    __shared__ uint64_t wn[kSelWaves], ws[kSelWaves];
+    __shared__ double wmax[kSelWaves];
+    __shared__ Split wbest[kSelWaves];
+    __shared__ int first_level;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int chunks = levels / 64;  // 4 or 1024
+    cn[tid] = cs[tid] = 0;
+    cmax[tid] = -1.0;
+    if (tid == 0) first_level = levels;
+    __syncthreads();
+    uint64_t q2 = 0;  // sigma: this lane's sum of c v^2 (below 2^64: fewer than 2^32 voxels)
+    for (int j0 = wave; j0 < chunks; j0 += 8 * kSelWaves) {
+        uint64_t c[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int j = j0 + i * kSelWaves;
+            c[i] = j < chunks ? hist[j * 64 + lane] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int j = j0 + i * kSelWaves, v = j * 64 + lane;
+            if (!__any(c[i] != 0)) continue;
+            if (c[i]) atomicMin(&first_level, v);
+            if (sigma) q2 += c[i] * (uint64_t)((uint32_t)v * (uint32_t)v);
+            const uint64_t n = wave_total(c[i]), s = wave_total(c[i] * (uint64_t)v);
+            if (lane == 0) {
+                cn[j] = n;
+                cs[j] = s;
+            }
+        }
+    }
+    __syncthreads();
+    // what precedes chunk tid, and the totals
+    const uint64_t n_own = cn[tid], s_own = cs[tid];
+    const uint64_t n_in = wave_scan(n_own, lane), s_in = wave_scan(s_own, lane);
+    if (lane == 63) {
+        wn[wave] = n_in;
+        ws[wave] = s_in;
+    }
+    __syncthreads();
+    uint64_t N = 0, S = 0, nb = 0, sb = 0;
+    for (int w = 0; w < kSelWaves; ++w) {
+        if (w == wave) {
+            nb = N;
+            sb = S;
+        }
+        N += wn[w];
+        S += ws[w];
+    }
+    cn[tid] = nb + n_in - n_own;
+    cs[tid] = sb + s_in - s_own;
+    if (sigma) {
+        // floor(2 sigma) = the largest w with w^2 N^2 <= 4 (N Q - S^2): the
+        // quotient's floor and its root's are the same integer
+        __shared__ uint64_t wq[kSelWaves];
+        const uint64_t q = wave_total(q2);
+        if (lane == 0) wq[wave] = q;
+        __syncthreads();
+        if (tid == 0) {
+            uint64_t Q = 0;
+            for (int w = 0; w < kSelWaves; ++w) Q += wq[w];
+            const u128 num = 4 * ((u128)N * Q - (u128)S * S), n2 = (u128)N * N;
+            uint32_t w = 0;
+            for (int b = 17; b >= 0; --b) {
+                const uint64_t x = w | (1u << b);
+                if (n2 * (x * x) <= num) w = (uint32_t)x;  // below 2^100
+            }
+            *dev = w;
+            *host = w;
+        }
+        return;
+    }
+    __syncthreads();
+    // criterion of every threshold that ends at an occupied level
+    auto split_of = [&](int j, uint64_t c) -> Split {
+        const int v = j * 64 + lane;
+        const Split x{cn[j] + wave_scan(c, lane), cs[j] + wave_scan(c * (uint64_t)v, lane), v + 1};
+        return (c == 0 || x.n0 == N) ? Split{0, 0, -1} : x;
+    };
+    auto criterion = [&](const Split& x) -> double {
+        if (x.t < 0) return -1.0;
+        const u128 p = (u128)N * x.s0, q = (u128)x.n0 * S, d = p >= q ? p - q : q - p;
+        const double df = (double)(uint64_t)(d >> 64) * 18446744073709551616.0 + (double)(uint64_t)d;
+        return df / ((double)x.n0 * (double)(N - x.n0)) * df;
+    };
+    double best = -1.0;
+    for (int j = wave; j < chunks; j += kSelWaves) {
+        const uint64_t c = hist[j * 64 + lane];
+        if (!__any(c != 0)) continue;
+        double v = criterion(split_of(j, c));
+        for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+        if (lane == 0) cmax[j] = v;
+        best = fmax(best, v);
+    }
+    if (lane == 0) wmax[wave] = best;
+    __syncthreads();
+    for (int w = 0; w < kSelWaves; ++w) best = fmax(best, wmax[w]);
+    const double near = best * (1.0 - 0x1p-40);
+    // exact comparison of the near ones, lowest threshold first
+    Split mine{0, 0, -1};
+    if (best >= 0.0) {
+        for (int j = wave; j < chunks; j += kSelWaves) {
+            if (cmax[j] < near) continue;  // the same for the whole wave
+            const Split x = split_of(j, hist[j * 64 + lane]);
+            if (criterion(x) >= near && (mine.t < 0 || split_better(x, mine, N, S))) mine = x;
+        }
+    }
+    // over the lanes: better, or equal and lower
+    auto take = [&](Split& a, const Split& b) {
+        if (b.t < 0) return;
+        if (a.t < 0 || split_better(b, a, N, S) || (!split_better(a, b, N, S) && b.t < a.t)) a = b;
+    };
+    if (__any(mine.t >= 0)) {
+        for (int off = 32; off > 0; off >>= 1) {
+            Split o;
+            o.n0 = __shfl_xor(mine.n0, off, 64);
+            o.s0 = __shfl_xor(mine.s0, off, 64);
+            o.t = __shfl_xor(mine.t, off, 64);
+            take(mine, o);
+        }
+    }
+    if (lane == 0) wbest[wave] = mine;
+    __syncthreads();
+    if (tid == 0) {
+        Split all{0, 0, -1};
+        for (int w = 0; w < kSelWaves; ++w) take(all, wbest[w]);
+        // fewer than two levels present: the present one, 0 for none
+        const uint32_t t = all.t >= 0 ? (uint32_t)all.t : first_level < levels ? (uint32_t)first_level : 0u;
+        *dev = t;
+        *host = t;
+    }
+}
+
 // ---- exact Otsu on the host ------------------------------------------------
 // Fixed-width unsigned integers of 12 x 64 bits (least significant limb
 // first): wide enough for every product below with counts up to 2^64.
@@ -205,10 +422,70 @@ namespace lnf {
 
 void otsu_scratch_free(lnf_ctx* h)
 {
+    for (ScalarSlot& s : h->scalar) {
+        if (s.done) {
+            if (s.pending) (void)hipEventSynchronize(s.done);
+            (void)hipEventDestroy(s.done);
+        }
+        if (s.ready) (void)hipEventDestroy(s.ready);
+        s = ScalarSlot{};
+    }
     if (h->otsu_dev) (void)hipFree(h->otsu_dev);
     if (h->otsu_host) (void)hipHostFree(h->otsu_host);
     h->otsu_dev = nullptr;
     h->otsu_host = nullptr;
+}
+
+int otsu_scratch(lnf_ctx* h)
+{
+    if (h->otsu_dev) return LNF_OK;
+    // the slots' values lie behind the 65536 counters, a cache line each
+    constexpr size_t kLine = 16, kWords = 65536 + kScalarSlots * kLine;
+    bool ok = hipMalloc((void**)&h->otsu_dev, kWords * sizeof(uint64_t)) == hipSuccess &&
+              hipHostMalloc((void**)&h->otsu_host, kWords * sizeof(uint64_t), hipHostMallocDefault) == hipSuccess;
+    for (int i = 0; ok && i < kScalarSlots; ++i) {
+        ScalarSlot& s = h->scalar[i];
+        s.dev = reinterpret_cast<uint32_t*>(h->otsu_dev + 65536 + i * kLine);
+        s.host = reinterpret_cast<uint32_t*>(h->otsu_host + 65536 + i * kLine);
+        ok = hipEventCreateWithFlags(&s.ready, hipEventDisableTiming) == hipSuccess &&
+             hipEventCreateWithFlags(&s.done, hipEventDisableTiming) == hipSuccess;
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        otsu_scratch_free(h);
+        return LNF_ENOMEM;
+    }
+    return LNF_OK;
+}
+
+int launch_scalar(lnf_ctx* h, const void* vol, size_t n, int dtype, bool sigma, hipStream_t stream,
+                  ScalarSlot** slot)
+{
+    // the value is waited for, which a capture cannot do
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return LNF_EHIP;
+    if (int rc = otsu_scratch(h)) return rc;
+    ScalarSlot& s = h->scalar[h->next_scalar];
+    h->next_scalar = (h->next_scalar + 1) % kScalarSlots;
+    if (s.pending && hipEventSynchronize(s.done) != hipSuccess) return LNF_EHIP;
+    s.pending = false;
+    const int levels = dtype == LNF_U8 ? 256 : 65536;
+    if (launch_histogram(vol, n, dtype, h->otsu_dev, stream) != hipSuccess) return LNF_EHIP;
+    hipLaunchKernelGGL(select_scalar, dim3(1), dim3(kSelThreads), 0, stream,
+                       reinterpret_cast<const unsigned long long*>(h->otsu_dev), levels, sigma ? 1 : 0, s.dev, s.host);
+    if (hipGetLastError() != hipSuccess || hipEventRecord(s.ready, stream) != hipSuccess) return LNF_EHIP;
+    *slot = &s;
+    return LNF_OK;
+}
+
+int finish_scalar(ScalarSlot* s, hipStream_t stream, uint32_t* value)
+{
+    // the caller may give the histogram scratch to another stream after this
+    if (hipEventRecord(s->done, stream) != hipSuccess) return LNF_EHIP;
+    s->pending = true;
+    if (hipEventSynchronize(s->ready) != hipSuccess) return LNF_EHIP;
+    *value = *static_cast<volatile uint32_t*>(s->host);
+    return LNF_OK;
 }
 
 }  // namespace lnf
@@ -253,26 +530,15 @@ extern "C" int lnf_filter_otsu(lnf_handle h, const void* vol, const int64_t dims
     if ((rc = check_device_range(vol, bytes, h->device))) return rc;
     if ((rc = check_device_range(out, bytes, h->device))) return rc;
     std::lock_guard<std::mutex> lk(h->otsu_mu);
-    if (!h->otsu_dev) {
-        if (hipMalloc((void**)&h->otsu_dev, 65536 * sizeof(uint64_t)) != hipSuccess ||
-            hipHostMalloc((void**)&h->otsu_host, 65536 * sizeof(uint64_t),
-                          hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            otsu_scratch_free(h);
-            return LNF_ENOMEM;
-        }
-    }
-    const int levels = dtype == LNF_U8 ? 256 : 65536;
-    const size_t n = (size_t)g.nx * g.ny * g.nz;
-    if (launch_histogram(vol, n, dtype, h->otsu_dev, stream) != hipSuccess) return LNF_EHIP;
-    if (hipMemcpyAsync(h->otsu_host, h->otsu_dev, levels * sizeof(uint64_t),
-                       hipMemcpyDeviceToHost, stream) != hipSuccess ||
-        hipStreamSynchronize(stream) != hipSuccess)
-        return LNF_EHIP;
-    const uint32_t t = otsu_from_hist(h->otsu_host, levels);
+    // the threshold stays on the device for the filter behind it; the host
+    // waits for its copy while the filter runs
+    ScalarSlot* slot = nullptr;
+    if ((rc = launch_scalar(h, vol, (size_t)g.nx * g.ny * g.nz, dtype, false, stream, &slot))) return rc;
+    const hipError_t e = launch_rule(h->rule, h->geom, vol, out, dtype, radius, g, 0,
+                                     ctx_tile(h, h->rule, dtype, radius, g), stream, nullptr, slot->dev);
+    uint32_t t = 0;
+    if ((rc = finish_scalar(slot, stream, &t))) return rc;
+    if (e != hipSuccess) return LNF_EHIP;
     if (T) *T = t;
-    if (launch_rule(h->rule, h->geom, vol, out, dtype, radius, g, t,
-                    ctx_tile(h, h->rule, dtype, radius, g), stream) != hipSuccess)
-        return LNF_EHIP;
     return LNF_OK;
 }

@@ -33,8 +33,11 @@ TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>&
 void mean9_tile_shape(int variant, int* tx, int* ty);
 // With plan != nullptr the launchers only resolve the configuration they
 // would launch (tile variant and z-strip depth) into *plan and launch nothing.
+// gate_dev, where not null, is a threshold in device memory that the kernel
+// reads instead of `gate`.
 hipError_t launch_mean9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
-                        TileCfg cfg, hipStream_t s, TileCfg* plan = nullptr);
+                        TileCfg cfg, hipStream_t s, TileCfg* plan = nullptr,
+                        const uint32_t* gate_dev = nullptr);
 // Whether rows are staged and stored as whole 32-bit words (WORDS in
 // mean9_tile.h).
 inline bool mean9_words_ok(const void* in, const void* out, int nx)
@@ -53,14 +56,17 @@ inline bool mean9_plane_ok(int dtype, Geom g)
 
 // ---- geometry variants (plane_tile.h): LNF_GEOM_* bits, both rules ---------
 hipError_t launch_geometry(int rule, uint32_t geom, const void* in, void* out, int dtype, int r,
-                           Geom g, uint32_t gate, int zs, hipStream_t s, TileCfg* plan = nullptr);
+                           Geom g, uint32_t gate, int zs, hipStream_t s, TileCfg* plan = nullptr,
+                        const uint32_t* gate_dev = nullptr);
 // The paper's mean filter (eq. 4): rounded mean of the (2r+1)^3 cube, gated.
 hipError_t launch_box_mean(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
                            hipStream_t s);
-// Sigma / Okada / entropy comparison filters (window.hip).
+// Sigma / Okada / entropy comparison filters (window.hip); param_dev, where not
+// null, is sigma's half width in device memory.
 constexpr int kWinSigma = 0, kWinOkada = 1, kWinEntropy = 2;
 hipError_t launch_window(int kind, const void* in, void* out, int dtype, int r, Geom g,
-                         int64_t param, const int64_t* weights, uint32_t gate, hipStream_t s);
+                         int64_t param, const int64_t* weights, uint32_t gate, hipStream_t s,
+                         const uint32_t* param_dev = nullptr);
 
 // ---- MINVAR9 (least-variance cluster) -------------------------------------
 int minvar9_variants();
@@ -68,7 +74,8 @@ int minvar9_variants();
 int minvar9_default_variant(int dtype, int r, Geom g);
 void minvar9_tile_shape(int variant, int r, int* tx, int* ty);  // output tile of (variant, r)
 hipError_t launch_minvar9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
-                          TileCfg cfg, hipStream_t s, TileCfg* plan = nullptr);
+                          TileCfg cfg, hipStream_t s, TileCfg* plan = nullptr,
+                        const uint32_t* gate_dev = nullptr);
 
 // Default z-strip depth: the strip count that minimises (rounds of
 // target_groups resident workgroups over tiles_xy * strips) x (strip depth +

@@ -29,8 +29,9 @@ template <int R, int TY, typename T, bool GATE, int TXW, bool BOX>
 __global__ __launch_bounds__((M9Geo<R, TY, TXW, T>::THREADS))
 __attribute__((amdgpu_waves_per_eu((m9_waves<R, TY, T>())))) void mean9_stream(
     const T* __restrict__ in, T* __restrict__ out, Geom g, int zs, int tiles_x, int tiles_y,
-    int total, uint32_t gate, double inv_div, int words)
+    int total, uint32_t gate, double inv_div, int words, const uint32_t* __restrict__ gate_dev)
 {
+    if (GATE && gate_dev) gate = *gate_dev;  // a threshold found on the device
     __shared__ __align__(16) M9Smem<R, TY, TXW, T> sm;
     const int tile = xcd_tile(blockIdx.x, total);
     const int bx = tile % tiles_x;
@@ -53,7 +54,7 @@ hipError_t launch_box(const T* in, T* out, Geom g, uint32_t gate, hipStream_t s)
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
     const int words = mean9_words_ok(in, out, g.nx) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(total), dim3(threads), 0, s, in, out, g, zs, tiles_x, tiles_y,
-                       total, gate, 1.0 / n, words);
+                       total, gate, 1.0 / n, words, (const uint32_t*)nullptr);
     return hipGetLastError();
 }
 
@@ -159,7 +160,8 @@ TileCfg resolve_tile(TileCfg want, int dtype, int r, Geom g)
 }
 
 template <int R, typename T, bool GATE, int TY, int TXW>
-hipError_t launch_stream(const T* in, T* out, Geom g, uint32_t gate, int zs, hipStream_t s)
+hipError_t launch_stream(const T* in, T* out, Geom g, uint32_t gate, int zs, hipStream_t s,
+                         const uint32_t* gate_dev)
 {
     constexpr int threads = M9Geo<R, TY, TXW, T>::THREADS;
     const auto kern = mean9_stream<R, TY, T, GATE, TXW, false>;
@@ -169,35 +171,36 @@ hipError_t launch_stream(const T* in, T* out, Geom g, uint32_t gate, int zs, hip
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
     const int words = mean9_words_ok(in, out, g.nx) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(total), dim3(threads), 0, s, in, out, g, zs, tiles_x, tiles_y,
-                       total, gate, 1.0 / (9.0 * n), words);
+                       total, gate, 1.0 / (9.0 * n), words, gate_dev);
     return hipGetLastError();
 }
 
 template <int R, typename T, bool GATE>
 hipError_t launch_variant(int variant, const void* in, void* out, Geom g, uint32_t gate, int zs,
-                          hipStream_t s)
+                          hipStream_t s, const uint32_t* gate_dev)
 {
     const T* pin = static_cast<const T*>(in);
     T* pout = static_cast<T*>(out);
     switch (variant) {
-    case 0: return launch_stream<R, T, GATE, 16, 64>(pin, pout, g, gate, zs, s);
-    case 1: return launch_stream<R, T, GATE, 32, 128>(pin, pout, g, gate, zs, s);
-    case 2: return launch_stream<R, T, GATE, 16, 32>(pin, pout, g, gate, zs, s);
-    default: return launch_stream<R, T, GATE, 16, 128>(pin, pout, g, gate, zs, s);
+    case 0: return launch_stream<R, T, GATE, 16, 64>(pin, pout, g, gate, zs, s, gate_dev);
+    case 1: return launch_stream<R, T, GATE, 32, 128>(pin, pout, g, gate, zs, s, gate_dev);
+    case 2: return launch_stream<R, T, GATE, 16, 32>(pin, pout, g, gate, zs, s, gate_dev);
+    default: return launch_stream<R, T, GATE, 16, 128>(pin, pout, g, gate, zs, s, gate_dev);
     }
 }
 
 template <int R, typename T>
 hipError_t launch_r(int variant, const void* in, void* out, Geom g, uint32_t gate, int zs,
-                    hipStream_t s)
+                    hipStream_t s, const uint32_t* gate_dev)
 {
-    if (gate) return launch_variant<R, T, true>(variant, in, out, g, gate, zs, s);
-    return launch_variant<R, T, false>(variant, in, out, g, gate, zs, s);
+    if (gate || gate_dev)
+        return launch_variant<R, T, true>(variant, in, out, g, gate, zs, s, gate_dev);
+    return launch_variant<R, T, false>(variant, in, out, g, gate, zs, s, nullptr);
 }
 
 template <typename T>
 hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, TileCfg cfg,
-                      hipStream_t s, TileCfg* plan)
+                      hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
     if (r < 1 || r > LNF_RADIUS_MAX) return hipErrorInvalidValue;
     cfg = resolve_tile(cfg, sizeof(T) == 1 ? LNF_U8 : LNF_U16, r, g);
@@ -207,10 +210,10 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
     }
     const int v = cfg.variant;
     switch (r) {
-    case 1: return launch_r<1, T>(v, in, out, g, gate, cfg.zs, s);
-    case 2: return launch_r<2, T>(v, in, out, g, gate, cfg.zs, s);
-    case 3: return launch_r<3, T>(v, in, out, g, gate, cfg.zs, s);
-    default: return launch_r<4, T>(v, in, out, g, gate, cfg.zs, s);
+    case 1: return launch_r<1, T>(v, in, out, g, gate, cfg.zs, s, gate_dev);
+    case 2: return launch_r<2, T>(v, in, out, g, gate, cfg.zs, s, gate_dev);
+    case 3: return launch_r<3, T>(v, in, out, g, gate, cfg.zs, s, gate_dev);
+    default: return launch_r<4, T>(v, in, out, g, gate, cfg.zs, s, gate_dev);
     }
 }
 
@@ -264,12 +267,13 @@ hipError_t launch_box_mean(const void* in, void* out, int dtype, int r, Geom g, 
 }
 
 hipError_t launch_mean9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
-                        TileCfg cfg, hipStream_t s, TileCfg* plan)
+                        TileCfg cfg, hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
     if (!plan && !mean9_plane_ok(dtype, g))
-        return launch_geometry(LNF_MEAN9, 0, in, out, dtype, r, g, gate, cfg.zs, s);
-    if (dtype == LNF_U8) return dispatch_r<uint8_t>(in, out, r, g, gate, cfg, s, plan);
-    return dispatch_r<uint16_t>(in, out, r, g, gate, cfg, s, plan);
+        return launch_geometry(LNF_MEAN9, 0, in, out, dtype, r, g, gate, cfg.zs, s, nullptr,
+                               gate_dev);
+    if (dtype == LNF_U8) return dispatch_r<uint8_t>(in, out, r, g, gate, cfg, s, plan, gate_dev);
+    return dispatch_r<uint16_t>(in, out, r, g, gate, cfg, s, plan, gate_dev);
 }
 
 }  // namespace lnf

@@ -11,8 +11,9 @@ template <int R, typename T, bool GATE, bool WT>
 __global__ __launch_bounds__((MV9Shape<R, WT>::THREADS))
 __attribute__((amdgpu_waves_per_eu(MV9Shape<R, WT>::WAVES))) void minvar9_planes(
     const T* __restrict__ in, T* __restrict__ out, Geom g, int zs, int tiles_x, int tiles_y,
-    int total, uint32_t gate, double dn, double invn)
+    int total, uint32_t gate, double dn, double invn, const uint32_t* __restrict__ gate_dev)
 {
+    if (GATE && gate_dev) gate = *gate_dev;  // a threshold found on the device
     using S = MV9Shape<R, WT>;
     __shared__ __align__(16) MV9Lds<R, T, WT> sm;
     const int tile = xcd_tile(blockIdx.x, total);
@@ -27,7 +28,7 @@ __attribute__((amdgpu_waves_per_eu(MV9Shape<R, WT>::WAVES))) void minvar9_planes
 
 template <int R, typename T, bool WT>
 hipError_t launch_planes(const void* in, void* out, Geom g, uint32_t gate, int zs, hipStream_t s,
-                         TileCfg* plan)
+                         TileCfg* plan, const uint32_t* gate_dev)
 {
     using S = MV9Shape<R, WT>;
     const int tiles_x = (g.nx + S::TX - 1) / S::TX, tiles_y = (g.ny + S::TY - 1) / S::TY;
@@ -43,35 +44,35 @@ hipError_t launch_planes(const void* in, void* out, Geom g, uint32_t gate, int z
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
     const T* pin = static_cast<const T*>(in);
     T* pout = static_cast<T*>(out);
-    if (gate)
+    if (gate || gate_dev)
         hipLaunchKernelGGL((minvar9_planes<R, T, true, WT>), dim3(total), dim3(S::THREADS), 0, s,
-                           pin, pout, g, zs, tiles_x, tiles_y, total, gate, (double)n, 1.0 / n);
+                           pin, pout, g, zs, tiles_x, tiles_y, total, gate, (double)n, 1.0 / n, gate_dev);
     else
         hipLaunchKernelGGL((minvar9_planes<R, T, false, WT>), dim3(total), dim3(S::THREADS), 0, s,
-                           pin, pout, g, zs, tiles_x, tiles_y, total, gate, (double)n, 1.0 / n);
+                           pin, pout, g, zs, tiles_x, tiles_y, total, gate, (double)n, 1.0 / n, gate_dev);
     return hipGetLastError();
 }
 
 template <int R, typename T>
 hipError_t launch_variant(int variant, const void* in, void* out, Geom g, uint32_t gate, int zs,
-                          hipStream_t s, TileCfg* plan)
+                          hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
-    if (variant == 1) return launch_planes<R, T, true>(in, out, g, gate, zs, s, plan);
-    return launch_planes<R, T, false>(in, out, g, gate, zs, s, plan);
+    if (variant == 1) return launch_planes<R, T, true>(in, out, g, gate, zs, s, plan, gate_dev);
+    return launch_planes<R, T, false>(in, out, g, gate, zs, s, plan, gate_dev);
 }
 
 template <typename T>
 hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, TileCfg cfg,
-                      hipStream_t s, TileCfg* plan)
+                      hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
     const int v = cfg.variant >= 0 ? cfg.variant
                                    : minvar9_default_variant(sizeof(T) == 1 ? LNF_U8 : LNF_U16, r, g);
     if (plan) plan->variant = v;
     switch (r) {
-    case 1: return launch_variant<1, T>(v, in, out, g, gate, cfg.zs, s, plan);
-    case 2: return launch_variant<2, T>(v, in, out, g, gate, cfg.zs, s, plan);
-    case 3: return launch_variant<3, T>(v, in, out, g, gate, cfg.zs, s, plan);
-    case 4: return launch_variant<4, T>(v, in, out, g, gate, cfg.zs, s, plan);
+    case 1: return launch_variant<1, T>(v, in, out, g, gate, cfg.zs, s, plan, gate_dev);
+    case 2: return launch_variant<2, T>(v, in, out, g, gate, cfg.zs, s, plan, gate_dev);
+    case 3: return launch_variant<3, T>(v, in, out, g, gate, cfg.zs, s, plan, gate_dev);
+    case 4: return launch_variant<4, T>(v, in, out, g, gate, cfg.zs, s, plan, gate_dev);
     default: return hipErrorInvalidValue;
     }
 }
@@ -101,10 +102,10 @@ void minvar9_tile_shape(int variant, int r, int* tx, int* ty)
 }
 
 hipError_t launch_minvar9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
-                          TileCfg cfg, hipStream_t s, TileCfg* plan)
+                          TileCfg cfg, hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
-    if (dtype == LNF_U8) return dispatch_r<uint8_t>(in, out, r, g, gate, cfg, s, plan);
-    return dispatch_r<uint16_t>(in, out, r, g, gate, cfg, s, plan);
+    if (dtype == LNF_U8) return dispatch_r<uint8_t>(in, out, r, g, gate, cfg, s, plan, gate_dev);
+    return dispatch_r<uint16_t>(in, out, r, g, gate, cfg, s, plan, gate_dev);
 }
 
 }  // namespace lnf

@@ -34,8 +34,10 @@ __global__ __launch_bounds__(kWThreads) void window_planes(const T* __restrict__
                                                            int tiles_x, int tiles_y, int total,
                                                            int64_t param,
                                                            const int64_t* __restrict__ weights,
-                                                           uint32_t gate)
+                                                           uint32_t gate,
+                                                           const uint32_t* __restrict__ param_dev)
 {
+    if (param_dev) param = *param_dev;  // sigma: a half width found on the device
     constexpr int LX = kWX + 2 * R, LY = kWY + 2 * R, NPL = 2 * R + 1;
     constexpr int NRAW = LX * LY, NLOAD = (NRAW + kWThreads - 1) / kWThreads;
     static_assert(KIND == kWinSigma || KIND == kWinOkada, "entropy runs on entropy_box");
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(kWThreads) void entropy_box(const T* __restrict__ i
 
 template <int R, typename T, int KIND>
 hipError_t launch_win(const void* in, void* out, Geom g, int64_t param, const int64_t* weights,
-                      uint32_t gate, hipStream_t s)
+                      uint32_t gate, hipStream_t s, const uint32_t* param_dev)
 {
     const auto kern = [] {
         if constexpr (KIND == kWinEntropy) return entropy_box<R, T>;
@@ -274,23 +276,29 @@ hipError_t launch_win(const void* in, void* out, Geom g, int64_t param, const in
     const int tiles_x = (g.nx + kWX - 1) / kWX, tiles_y = (g.ny + kWY - 1) / kWY;
     const int zs = default_zs(tiles_x * tiles_y, g.nz, resident_groups((const void*)kern, 256));
     const int total = tiles_x * tiles_y * ((g.nz + zs - 1) / zs);
-    hipLaunchKernelGGL(kern, dim3(total), dim3(kWThreads), 0, s, static_cast<const T*>(in),
-                       static_cast<T*>(out), g, zs, tiles_x, tiles_y, total, param, weights, gate);
+    if constexpr (KIND == kWinEntropy)
+        hipLaunchKernelGGL(kern, dim3(total), dim3(kWThreads), 0, s, static_cast<const T*>(in),
+                           static_cast<T*>(out), g, zs, tiles_x, tiles_y, total, param, weights, gate);
+    else
+        hipLaunchKernelGGL(kern, dim3(total), dim3(kWThreads), 0, s, static_cast<const T*>(in),
+                           static_cast<T*>(out), g, zs, tiles_x, tiles_y, total, param, weights, gate,
+                           param_dev);
     return hipGetLastError();
 }
 
 template <typename T, int KIND>
 hipError_t dispatch_win(int r, const void* in, void* out, Geom g, int64_t param,
-                        const int64_t* weights, uint32_t gate, hipStream_t s)
+                        const int64_t* weights, uint32_t gate, hipStream_t s,
+                        const uint32_t* param_dev)
 {
     if constexpr (KIND == kWinOkada) {
-        return launch_win<1, T, KIND>(in, out, g, param, weights, gate, s);
+        return launch_win<1, T, KIND>(in, out, g, param, weights, gate, s, param_dev);
     } else {
         switch (r) {
-        case 1: return launch_win<1, T, KIND>(in, out, g, param, weights, gate, s);
-        case 2: return launch_win<2, T, KIND>(in, out, g, param, weights, gate, s);
-        case 3: return launch_win<3, T, KIND>(in, out, g, param, weights, gate, s);
-        case 4: return launch_win<4, T, KIND>(in, out, g, param, weights, gate, s);
+        case 1: return launch_win<1, T, KIND>(in, out, g, param, weights, gate, s, param_dev);
+        case 2: return launch_win<2, T, KIND>(in, out, g, param, weights, gate, s, param_dev);
+        case 3: return launch_win<3, T, KIND>(in, out, g, param, weights, gate, s, param_dev);
+        case 4: return launch_win<4, T, KIND>(in, out, g, param, weights, gate, s, param_dev);
         default: return hipErrorInvalidValue;
         }
     }
@@ -298,37 +306,21 @@ hipError_t dispatch_win(int r, const void* in, void* out, Geom g, int64_t param,
 
 template <typename T>
 hipError_t dispatch_kind(int kind, int r, const void* in, void* out, Geom g, int64_t param,
-                         const int64_t* weights, uint32_t gate, hipStream_t s)
+                         const int64_t* weights, uint32_t gate, hipStream_t s,
+                        const uint32_t* param_dev)
 {
     switch (kind) {
-    case kWinSigma: return dispatch_win<T, kWinSigma>(r, in, out, g, param, weights, gate, s);
-    case kWinOkada: return dispatch_win<T, kWinOkada>(r, in, out, g, param, weights, gate, s);
-    default: return dispatch_win<T, kWinEntropy>(r, in, out, g, param, weights, gate, s);
+    case kWinSigma: return dispatch_win<T, kWinSigma>(r, in, out, g, param, weights, gate, s, param_dev);
+    case kWinOkada: return dispatch_win<T, kWinOkada>(r, in, out, g, param, weights, gate, s, param_dev);
+    default: return dispatch_win<T, kWinEntropy>(r, in, out, g, param, weights, gate, s, param_dev);
     }
-}
-
-// floor(sqrt(n)) for n < 2^64
-uint64_t isqrt64(unsigned __int128 n)
-{
-    uint64_t x = (uint64_t)std::sqrt((double)n);
-    while ((unsigned __int128)x * x > n) --x;
-    while ((unsigned __int128)(x + 1) * (x + 1) <= n) ++x;
-    return x;
 }
 
 // Histogram of the volume into the context's scratch, copied to the host
 // (synchronises `stream`).  Caller holds h->otsu_mu.
 int host_histogram(lnf_ctx* h, const void* vol, size_t n, int dtype, hipStream_t stream)
 {
-    if (!h->otsu_dev) {
-        if (hipMalloc((void**)&h->otsu_dev, 65536 * sizeof(uint64_t)) != hipSuccess ||
-            hipHostMalloc((void**)&h->otsu_host, 65536 * sizeof(uint64_t),
-                          hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            otsu_scratch_free(h);
-            return LNF_ENOMEM;
-        }
-    }
+    if (int rc = otsu_scratch(h)) return rc;
     const int levels = dtype == LNF_U8 ? 256 : 65536;
     if (launch_histogram(vol, n, dtype, h->otsu_dev, stream) != hipSuccess ||
         hipMemcpyAsync(h->otsu_host, h->otsu_dev, levels * sizeof(uint64_t),
@@ -350,10 +342,11 @@ int check_pair(lnf_handle h, const void* vol, const int64_t* dims, int dtype, in
 }  // namespace
 
 hipError_t launch_window(int kind, const void* in, void* out, int dtype, int r, Geom g,
-                         int64_t param, const int64_t* weights, uint32_t gate, hipStream_t s)
+                         int64_t param, const int64_t* weights, uint32_t gate, hipStream_t s,
+                        const uint32_t* param_dev)
 {
-    if (dtype == LNF_U8) return dispatch_kind<uint8_t>(kind, r, in, out, g, param, weights, gate, s);
-    return dispatch_kind<uint16_t>(kind, r, in, out, g, param, weights, gate, s);
+    if (dtype == LNF_U8) return dispatch_kind<uint8_t>(kind, r, in, out, g, param, weights, gate, s, param_dev);
+    return dispatch_kind<uint16_t>(kind, r, in, out, g, param, weights, gate, s, param_dev);
 }
 
 void entropy_scratch_free(lnf_ctx* h)
@@ -391,30 +384,28 @@ extern "C" int lnf_filter_sigma(lnf_handle h, const void* vol, const int64_t dim
     if (!dg.ok()) return LNF_EHIP;
     int rc = check_pair(h, vol, dims, dtype, radius, out, &g, &bytes);
     if (rc) return rc;
-    int64_t w = half_width;
-    if (w < 0) {  // floor(2 sigma) of the whole volume, exact
-        std::lock_guard<std::mutex> lk(h->otsu_mu);
-        const size_t n = (size_t)g.nx * g.ny * g.nz;
-        if ((rc = host_histogram(h, vol, n, dtype, stream))) return rc;
-        const int levels = dtype == LNF_U8 ? 256 : 65536;
-        unsigned __int128 N = 0, S = 0, Q = 0;
-        for (int l = 0; l < levels; ++l) {
-            const unsigned __int128 c = h->otsu_host[l];
-            N += c;
-            S += c * (unsigned)l;
-            Q += c * (unsigned)l * (unsigned)l;
-        }
-        // (2 sigma)^2 = 4 (N Q - S^2) / N^2; floor(sqrt(a / b)) = isqrt(floor(a / b));
-        // with N < 2^32, N Q < 2^96 and S^2 < 2^96 fit the 128-bit arithmetic
-        if (N == 0 || N >> 32) return LNF_EINVAL;  // exact only below 2^32 voxels
-        const unsigned __int128 num = 4 * (N * Q - S * S);
-        w = (int64_t)isqrt64(num / (N * N));
+    if (half_width >= 0) {
+        if (used_half_width) *used_half_width = half_width;
+        return launch_window(kWinSigma, vol, out, dtype, radius, g, half_width, nullptr, h->gate, stream) ==
+                       hipSuccess
+                   ? LNF_OK
+                   : LNF_EHIP;
     }
+    // floor(2 sigma) of the whole volume, exact below 2^32 voxels: found on the
+    // device, where the filter behind it reads it; the host waits for its copy
+    // while the filter runs
+    const size_t n = (size_t)g.nx * g.ny * g.nz;
+    if (n >> 32) return LNF_EINVAL;
+    std::lock_guard<std::mutex> lk(h->otsu_mu);
+    ScalarSlot* slot = nullptr;
+    if ((rc = launch_scalar(h, vol, n, dtype, true, stream, &slot))) return rc;
+    const hipError_t e = launch_window(kWinSigma, vol, out, dtype, radius, g, 0, nullptr, h->gate, stream,
+                                       slot->dev);
+    uint32_t w = 0;
+    if ((rc = finish_scalar(slot, stream, &w))) return rc;
+    if (e != hipSuccess) return LNF_EHIP;
     if (used_half_width) *used_half_width = w;
-    return launch_window(kWinSigma, vol, out, dtype, radius, g, w, nullptr, h->gate, stream) ==
-                   hipSuccess
-               ? LNF_OK
-               : LNF_EHIP;
+    return LNF_OK;
 }
 
 extern "C" int lnf_filter_okada(lnf_handle h, const void* vol, const int64_t dims[3], int dtype,

@@ -113,3 +113,68 @@ def test_points_at_faces_and_alignments(dt, r):
                     got = f.points(dev, r, xyz).cpu().numpy().view(np.uint32)
                     assert np.array_equal(got, want[sel]), (dims, rule, lead, n)
             f.close()
+
+
+# ---- Otsu's threshold and 2 sigma, found on the device ------------------------
+
+def _levels(dt, kind):
+    top = int(np.iinfo(dt).max)
+    rng = np.random.default_rng(99)
+    if kind == "one":
+        v = np.full(60, top)
+    elif kind == "two":
+        v = np.array([0, top] * 30)
+    elif kind == "ties":   # symmetric: several thresholds with the same criterion
+        v = np.array([0, 1, top - 1, top] * 15)
+    elif kind == "every":  # every level once
+        v = np.arange(top + 1)
+    elif kind == "chunks":  # at the edges of groups of 64 levels
+        v = rng.choice(np.array([0, 63, 64, 65, 127, 128, 191, 192, top - 63, top]), 4096)
+    else:                  # few levels, uneven counts
+        v = rng.choice(rng.integers(0, top + 1, 7), 1001, p=[.5, .2, .1, .1, .05, .04, .01])
+    return v.astype(dt)
+
+
+@pytest.mark.parametrize("kind", ["one", "two", "ties", "every", "chunks", "few"])
+@pytest.mark.parametrize("dt", [np.uint8, np.uint16])
+def test_threshold_and_half_width_on_the_device(dt, kind):
+    from oracle import otsu as ootsu
+    from paper_1807_03119_amd.api import Filter
+    v = _levels(dt, kind)
+    vol = np.ascontiguousarray(v.reshape(1, 1, -1) if v.size % 4 else v.reshape(2, 2, -1))
+    dev = torch.from_numpy(vol).cuda()
+    counts = np.bincount(v, minlength=int(np.iinfo(dt).max) + 1)
+    want_t = ootsu.otsu_threshold(counts)
+    want_w = ocmp.sigma_half_width(vol)
+    for rule, orule in ((_lib.LNF_MEAN9, oracle.MEAN9), (_lib.LNF_MINVAR9, oracle.MINVAR9)):
+        f = Filter(rule, 0)
+        out, t = f.filter_otsu(dev, 1)
+        assert t == want_t
+        assert np.array_equal(out.cpu().numpy(), oracle.filter_volume(vol, 1, orule, t))
+        out, w = f.sigma(dev, 1)
+        assert w == want_w
+        assert np.array_equal(out.cpu().numpy(), ocmp.sigma_filter(vol, 1))
+        f.close()
+
+
+def test_otsu_calls_in_flight_on_several_streams():
+    """More calls in flight than the context keeps threshold slots: each filter
+    is gated at its own volume's threshold."""
+    from oracle import otsu as ootsu
+    from paper_1807_03119_amd.api import Filter
+    f = Filter(_lib.LNF_MEAN9, 0)
+    rng = np.random.default_rng(5)
+    vols = [(rng.integers(0, 2, (24, 40, 50)) * (k + 1) * 900 + 100 * k).astype(np.uint16) for k in range(24)]
+    devs = [torch.from_numpy(v).cuda() for v in vols]
+    outs = [torch.empty_like(d) for d in devs]
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    ts = []
+    for k, d in enumerate(devs):
+        with torch.cuda.stream(streams[k % 3]):
+            ts.append(f.filter_otsu(d, 2, out=outs[k])[1])
+    torch.cuda.synchronize()
+    for v, o, t in zip(vols, outs, ts):
+        assert t == ootsu.otsu_threshold(np.bincount(v.ravel(), minlength=65536))
+        assert np.array_equal(o.cpu().numpy(), oracle.filter_volume(v, 2, oracle.MEAN9, t))
+    f.close()
