@@ -83,11 +83,12 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
 // r = 3; the same tile as 0 at r = 4)
 int minvar9_variants() { return 2; }
 
-// The wide tile on large planes where it measured faster (uint16 up to r = 3,
-// uint8 at r = 3), else 32 x 16.
+// The wide tile on large planes up to r = 3 (uint8: r = 1 274 -> 257 us, r = 2
+// 365 -> 352 on 512^3), else 32 x 16.
 int minvar9_default_variant(int dtype, int r, Geom g)
 {
-    return (g.nx >= 256 && g.ny >= 256 && r <= 3 && (dtype == LNF_U16 || r == 3)) ? 1 : 0;
+    (void)dtype;
+    return (g.nx >= 256 && g.ny >= 256 && r <= 3) ? 1 : 0;
 }
 
 void minvar9_tile_shape(int variant, int r, int* tx, int* ty)

@@ -193,23 +193,53 @@ struct PTSmem {
     static constexpr double VMAX = sizeof(T) == 1 ? 255.0 : 65535.0;
     static constexpr bool PACK =
         VAR && (double)S::N * S::N * VMAX * VMAX / 4.0 < 281474976710656.0;  // 2^48
+    // Ordered keys: where v fits 42 bits (uint8, narrow squares), a key is v *
+    // 2^18 + rounded mean (14 bits), and the gather puts the cluster's index
+    // into the four bits between them.  The first minimum is then a plain
+    // minimum, and, the keys being positive fp64 bit patterns, one instruction.
+    static constexpr double VLIM = sizeof(T) == 1 ? 255.0 : (double)((1 << nq_bits(R)) - 1);
+    static constexpr bool ORD = PACK && (NQ || sizeof(T) == 1);
+    static_assert(!ORD || (double)S::N * S::N * VLIM * VLIM / 4.0 < 4398046511104.0, "v < 2^42");
+    // Paired sums (cubes with 32-bit sums of squares, from r = 2): the sum and
+    // the sum of squares of a column lie side by side in the z-sums and in the
+    // x-pass output, so each is written and read with one 8-byte access.  LDS is
+    // what bounds these tiles (64 x 16, r = 3: busy 92 % of the time), and a
+    // wave's 4-byte access takes it as long as an 8-byte one.  At r = 1 the x-
+    // passes of the sums and of the squares on separate waves are faster (308
+    // against 339 us).
+    static constexpr bool PAIR = VAR && !CROSS && !WIDE && R >= 2;
+    // pairs of a row; 2 mod 4, so that eight rows of a 16-byte read start in
+    // distinct bank groups
+    static constexpr int ZP2 = S::LX + (6 - S::LX % 4) % 4;
+    static constexpr int ZN2 = ((S::LY - 1) * ZP2 + (S::NXS - 1) * S::XS + S::XW + 2) / 2 * 2;
     static constexpr int XPQ = WIDE ? S::XPD : S::XPB;
     // every array a multiple of 16 bytes, so each starts 16-byte aligned
     static constexpr int a16(int n, int bytes) { return (n * bytes + 15) / 16 * 16 / bytes; }
     static constexpr int QN = VAR ? 1 : 0, CN = CROSS ? 1 : 0;
-    QT xq[QN ? a16(S::XROWS * XPQ, sizeof(QT)) : a16(1, sizeof(QT))];
+    QT xq[PAIR ? 2 * a16(S::XROWS * S::XPD, sizeof(QT)) : QN ? a16(S::XROWS * XPQ, sizeof(QT)) : a16(1, sizeof(QT))];
     QT yq[QN * CN ? a16(S::XROWS * XPQ, sizeof(QT)) : a16(1, sizeof(QT))];  // crosses: y-lines of E^2
-    // MINVAR9: v, or the packed keys (two planes for NQ from r = 2, whose
-    // tile body gathers from one plane while the next is written)
-    double vv[QN ? (NQ && R >= 2 ? 2 : 1) * a16(S::GY * S::VP, 8) : 2];
-    uint32_t zb[S::ZN];
-    uint32_t zq0[QN ? S::ZN : 4];                // uint8: Zq; uint16: low half of Zq
+    // MINVAR9: v, or the packed keys (two planes for the pipelined tiles,
+    // which gather from one plane while the next is written)
+    static constexpr bool PIPE = VAR && !CROSS && D == R && R >= 2 && (NQ || sizeof(T) == 1);
+    double vv[QN ? (PIPE ? 2 : 1) * a16(S::GY * S::VP, 8) : 2];
+    uint32_t zb[PAIR ? 2 * ZN2 : S::ZN];         // PAIR: (sum, sum of squares) of each column
+    uint32_t zq0[QN && !PAIR ? S::ZN : 4];                // uint8: Zq; uint16: low half of Zq
     uint32_t zq1[QN && WIDE ? S::ZN : 4];        // uint16: high half of Zq
     uint32_t ec[CN ? S::ZN : 4];                 // crosses: slice p
-    uint32_t xb[a16(S::XROWS * S::XPB, 4)];      // cubes: x-pass; crosses: x-lines
+    uint32_t xb[PAIR ? 4 : a16(S::XROWS * S::XPB, 4)];  // cubes: x-pass; crosses: x-lines
     uint32_t yb[CN ? a16(S::XROWS * S::XPB, 4) : 4];  // crosses: y-lines
     uint32_t vo[PACK ? 4 : a16(S::GY * S::VP, 4)];  // MINVAR9: rounded means; MEAN9: B
 };
+
+// The lower of two ordered keys (positive, normal fp64 bit patterns).
+__device__ __forceinline__ uint64_t min_key(uint64_t a, uint64_t b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2"
+        : "=v"(r)
+        : "v"(__builtin_bit_cast(double, a)), "v"(__builtin_bit_cast(double, b)));
+    return __builtin_bit_cast(uint64_t, r);
+}
 
 // dn = n; inv = 1/n (MINVAR9) or 1/(9n) (MEAN9); tid: threadIdx.x (see
 // tile_tid for loops over several tiles).  NQ: narrow sums of squares; `flag`
@@ -227,7 +257,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
     using SM = PTSmem<R, D, SHAPE, RULE, T, WT, NQ>;
     using QT = typename SM::QT;
     using YQ = typename SM::YQ;
-    constexpr bool VAR = S::VAR, CROSS = S::CROSS, WIDE = SM::WIDE, PACK = SM::PACK;
+    constexpr bool VAR = S::VAR, CROSS = S::CROSS, WIDE = SM::WIDE, PACK = SM::PACK, PAIR = SM::PAIR;
     static_assert(!NQ || (VAR && !CROSS && sizeof(T) == 2 && PACK),
                   "narrow squares: MINVAR9 cubes, uint16, packed keys");
     constexpr uint32_t kNQLimit = 1u << nq_bits(R);
@@ -242,7 +272,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
     const uint32_t pbytes = (uint32_t)(plane * sizeof(T));
 
     // NQ tiles from r = 2 run as a two-barrier pipeline (below)
-    constexpr bool PIPE = NQ && R >= 2;
+    constexpr bool PIPE = SM::PIPE;
     // ---- raw columns owned for the z-sums.  Pipelined tiles rotate them so
     // that the partial last round falls on the highest threads, whose waves
     // have no y-pass work in the same phase.
@@ -256,7 +286,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
         const int row = e / LX, col = e - row * LX;
         off[i] = (uint32_t)(clampi(y0 - S::E + row, 0, g.ny - 1) * g.nx +
                             clampi(x0 - S::E + col, 0, g.nx - 1)) * (uint32_t)sizeof(T);
-        zi[i] = row * S::ZP + col;
+        zi[i] = PAIR ? 2 * (row * SM::ZP2 + col) : row * S::ZP + col;
     }
     // lanes past the tile in the last round own no column
     const bool zlast = zt + (S::NZ - 1) * kT < S::NRAW;
@@ -323,6 +353,12 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
         }
     uint64_t* const keys = reinterpret_cast<uint64_t*>(sm.vv);
     constexpr uint64_t kHigh = ~0xffffull;  // a key's v part (key & kHigh = v * 2^16)
+    constexpr bool ORD = SM::ORD;
+    // 2^52 + v as an fp64 value has v in its mantissa field; ordered keys add
+    // 2^42, which makes every key a normal number
+    constexpr double kKeyBase = ORD ? 0x1p52 + 0x1p42 : 0x1p52;
+    constexpr int kKeyShift = ORD ? 18 : 16;
+    constexpr uint64_t kUpper = 4ull << 14;  // from the lower plane's indices to the upper's
 
     // y-pass mapping: consecutive lanes take consecutive centre columns
     const int ycol = tid % GX, yseg = tid / GX;
@@ -339,6 +375,43 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
             const int xrow = it % S::XR, xseg = it / S::XR;
             if (xrow >= S::XIN) continue;
             const int cbase = xseg * XS;
+            if constexpr (PAIR) {
+                // running windows over the row's pairs
+                static_assert(S::XW % 2 == 0, "whole 16-byte reads");
+                uint32_t b[S::XW], q[S::XW];
+                const uint4* sp = reinterpret_cast<const uint4*>(sm.zb + 2 * (xrow * SM::ZP2 + cbase));
+#pragma unroll
+                for (int i = 0; i < S::XW; i += 2) {
+                    const uint4 t = sp[i / 2];
+                    b[i] = t.x;
+                    q[i] = t.y;
+                    b[i + 1] = t.z;
+                    q[i + 1] = t.w;
+                }
+                uint32_t rb = b[0], rq = q[0];
+#pragma unroll
+                for (int i = 1; i <= 2 * R; ++i) {
+                    rb += b[i];
+                    rq += q[i];
+                }
+                uint4* dp = reinterpret_cast<uint4*>(sm.xq + 2 * (xrow * S::XPD + cbase));
+#pragma unroll
+                for (int m = 0; m < XS; m += 2) {
+                    uint4 t;
+                    t.x = rb;
+                    t.y = rq;
+                    rb += b[m + 1 + 2 * R] - b[m];
+                    rq += q[m + 1 + 2 * R] - q[m];
+                    t.z = rb;
+                    t.w = rq;
+                    dp[m / 2] = t;
+                    if (m + 2 < XS) {
+                        rb += b[m + 2 + 2 * R] - b[m + 1];
+                        rq += q[m + 2 + 2 * R] - q[m + 1];
+                    }
+                }
+                continue;
+            }
             const int zr = (S::XROW0 + xrow) * S::ZP + cbase;
             // sums first, then squares: one row segment live at a time keeps
             // the x-pass within the 4-waves-per-SIMD register budget
@@ -403,7 +476,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
         }
     };
     auto xpass = [&](const uint32_t* src, const uint32_t* src0, const uint32_t* src1) {
-        if constexpr (S::XSPLIT) {
+        if constexpr (S::XSPLIT && !PAIR) {
             if (tid < S::QOFF) xpass_items(src, src0, src1, tid, true, false);
             else xpass_items(src, src0, src1, tid - S::QOFF, false, true);
         } else {
@@ -416,9 +489,9 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
         if constexpr (PACK) {
             // v + 2^52 is exact (v < 2^48), so its mantissa field is v
             const double db = (double)b;
-            const double vb = __builtin_fma(dn, (double)qv, __builtin_fma(-db, db, 0x1p52));
+            const double vb = __builtin_fma(dn, (double)qv, __builtin_fma(-db, db, kKeyBase));
             const uint64_t v = __builtin_bit_cast(uint64_t, vb) & ((1ull << 52) - 1);
-            keys[gy * VP + gx] = (v << 16) | round_div_odd(b, inv);
+            keys[gy * VP + gx] = (v << kKeyShift) | round_div_odd(b, inv);
         } else if constexpr (VAR) {
             const double db = (double)b;
             sm.vv[gy * VP + gx] = __builtin_fma(dn, (double)qv, -db * db);
@@ -445,9 +518,9 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
         // the packed key of one centre, written to plane kb
         auto centre_key = [&](uint64_t* kb, int gy, int gx, uint32_t b, YQ qv) {
             const double db = (double)b;
-            const double vb = __builtin_fma(dn, (double)qv, __builtin_fma(-db, db, 0x1p52));
+            const double vb = __builtin_fma(dn, (double)qv, __builtin_fma(-db, db, kKeyBase));
             const uint64_t v = __builtin_bit_cast(uint64_t, vb) & ((1ull << 52) - 1);
-            kb[gy * VP + gx] = (v << 16) | round_div_odd(b, inv);
+            kb[gy * VP + gx] = (v << kKeyShift) | round_div_odd(b, inv);
         };
         // cluster sums at every centre of the region, as keys in plane kb
         auto ypass_cubes = [&](uint64_t* kb) {
@@ -458,6 +531,12 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                 YQ cq[S::YW];
 #pragma unroll
                 for (int t = 0; t < S::YW; ++t) {
+                    if constexpr (PAIR) {
+                        const uint2 bq = *reinterpret_cast<const uint2*>(sm.xq + 2 * ((rbase + t) * S::XPD + ycol));
+                        cb[t] = t ? cb[t - 1] + bq.x : bq.x;
+                        cq[t] = t ? cq[t - 1] + (YQ)bq.y : (YQ)bq.y;
+                        continue;
+                    }
                     const uint32_t b = sm.xb[(rbase + t) * S::XPB + ycol];
                     cb[t] = t ? cb[t - 1] + b : b;
                     if constexpr (VAR) {
@@ -489,7 +568,19 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                 const int oy = oyb + j * S::OROWS;
                 const int ic = (oy + D) * VP + ox + D;
                 uint32_t o;
-                if constexpr (PACK) {
+                if constexpr (ORD) {
+                    // cluster 0 is the centre, 1..4 the plane below, 5..8 above
+                    const uint64_t ck = kb[ic];
+                    uint64_t gk = kb[oy * VP + ox] | (1ull << 14);
+#pragma unroll
+                    for (int k = 1; k < 4; ++k) {
+                        const int ik = (oy + ((k & 2) ? 2 * D : 0)) * VP + ox + ((k & 1) ? 2 * D : 0);
+                        gk = min_key(gk, kb[ik] | ((uint64_t)(k + 1) << 14));
+                    }
+                    o = (uint32_t)min_key(mk[ur][j], gk + kUpper) & 0x3fffu;
+                    mk[u][j] = min_key(ck, ak[ur][j]);
+                    ak[u][j] = gk;
+                } else if constexpr (PACK) {
                     // c.v < b.v  <=>  c.key < (b.key & kHigh): the same
                     // first minima as the unpacked branch below
                     const uint64_t ck = kb[ic];
@@ -562,6 +653,10 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
 #pragma unroll
                 for (int i = 0; i < S::NZ; ++i) {
                     if (i < S::NZ - 1 || zlast) {
+                        if constexpr (PAIR) {
+                            *reinterpret_cast<uint2*>(sm.zb + zi[i]) = make_uint2(zb[i], (uint32_t)zq[i]);
+                            continue;
+                        }
                         sm.zb[zi[i]] = zb[i];
                         if constexpr (VAR) {
                             if constexpr (WIDE) {
@@ -647,6 +742,10 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
 #pragma unroll
                 for (int i = 0; i < S::NZ; ++i) {
                     if (i < S::NZ - 1 || zlast) {
+                        if constexpr (PAIR) {
+                            *reinterpret_cast<uint2*>(sm.zb + zi[i]) = make_uint2(zb[i], (uint32_t)zq[i]);
+                            continue;
+                        }
                         sm.zb[zi[i]] = zb[i];
                         if constexpr (VAR) {
                             if constexpr (WIDE) {
@@ -712,6 +811,12 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                         YQ cq[S::YW];
 #pragma unroll
                         for (int t = 0; t < S::YW; ++t) {
+                            if constexpr (PAIR) {
+                                const uint2 bq = *reinterpret_cast<const uint2*>(sm.xq + 2 * ((rbase + t) * S::XPD + ycol));
+                                cb[t] = t ? cb[t - 1] + bq.x : bq.x;
+                                cq[t] = t ? cq[t - 1] + (YQ)bq.y : (YQ)bq.y;
+                                continue;
+                            }
                             const uint32_t b = sm.xb[(rbase + t) * S::XPB + ycol];
                             cb[t] = t ? cb[t - 1] + b : b;
                             if constexpr (VAR) {
@@ -762,7 +867,19 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                     const int oy = oyb + j * S::OROWS;
                     const int ic = (oy + D) * VP + ox + D;
                     uint32_t o;
-                    if constexpr (PACK) {
+                    if constexpr (ORD) {
+                        // cluster 0 is the centre, 1..4 the plane below, 5..8 above
+                        const uint64_t ck = keys[ic];
+                        uint64_t gk = keys[oy * VP + ox] | (1ull << 14);
+#pragma unroll
+                        for (int k = 1; k < 4; ++k) {
+                            const int ik = (oy + ((k & 2) ? 2 * D : 0)) * VP + ox + ((k & 1) ? 2 * D : 0);
+                            gk = min_key(gk, keys[ik] | ((uint64_t)(k + 1) << 14));
+                        }
+                        o = (uint32_t)min_key(mk[ur][j], gk + kUpper) & 0x3fffu;
+                        mk[u][j] = min_key(ck, ak[ur][j]);
+                        ak[u][j] = gk;
+                    } else if constexpr (PACK) {
                         // c.v < b.v  <=>  c.key < (b.key & kHigh): the same
                         // first minima as the unpacked branch below
                         const uint64_t ck = keys[ic];
