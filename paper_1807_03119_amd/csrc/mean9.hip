@@ -94,9 +94,9 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 struct TileCost {
     int one, more, resident;
 };
-constexpr TileCost kCostU16[2][kNumVariants] = {{{38, 22, 3}, {116, 0, 1}, {36, 12, 6}, {66, 0, 1}},
+constexpr TileCost kCostU16[2][kNumVariants] = {{{38, 22, 3}, {104, 0, 1}, {36, 12, 6}, {64, 0, 1}},
                                                 {{36, 20, 3}, {84, 0, 1}, {33, 12, 6}, {50, 0, 1}}};
-constexpr TileCost kCostU8[2][kNumVariants] = {{{30, 16, 4}, {74, 0, 1}, {28, 8, 8}, {44, 20, 2}},
+constexpr TileCost kCostU8[2][kNumVariants] = {{{30, 16, 4}, {62, 0, 1}, {28, 8, 8}, {44, 20, 2}},
                                                {{28, 14, 4}, {48, 0, 1}, {26, 8, 8}, {36, 20, 2}}};
 // At r = 4 the rings take more registers, so fewer workgroups are resident.
 constexpr int kResidentU16R4[kNumVariants] = {2, 1, 4, 1}, kResidentU8R4[kNumVariants] = {3, 1, 6, 1};

@@ -233,40 +233,89 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
     constexpr float kP = -1152.f * (2 * R + 1), kQ = SPLIT ? kP : 2.f * kP;
     const f32x4_t cp = {kP, kP, kP, kP}, cq = {kQ, kQ, kQ, kQ}, zero = {0.f, 0.f, 0.f, 0.f};
 
-    // ---- outputs as stored: whole words, 4 columns per thread and TXW / 4
-    // adjacent threads to a row; or voxels, TXW threads to a row.  Outputs
-    // outside the volume get the plane size as their offset, and slices that
+    // ---- outputs as stored.  WORDS: 4 columns per thread, TXW / 4 adjacent
+    // threads to a row.  Otherwise tiles 128 wide store the whole 8-byte pieces
+    // of a row from its first aligned word on (shifted out of the LDS words that
+    // hold them), and what is left at its two ends voxel by voxel, sixteen
+    // threads to a row (511 x 512 x 512 uint16, r = 3, 128 x 32 tiles: 175 -> 156
+    // us against voxel by voxel); narrower tiles, whose rows have more ends,
+    // store voxel by voxel (64 x 16: 200 us against 228).
+    // Outputs outside the volume get an offset past its end, and slices that
     // are not the strip's an empty buffer resource: either is dropped by the
     // range check, so every iteration issues the same memory operations and
     // its waits can leave the younger ones in flight.
-    constexpr int kPer = WORDS ? 4 : 1, kRows = kT * kPer / TXW, kStores = TY / kRows;
-    const int sc = kPer * (tid % (TXW / kPer)), srow = tid / (TXW / kPer);
-    const uint32_t sbase = ((uint32_t)(y0 + srow) * (uint32_t)nx + (uint32_t)(x0 + sc)) * (uint32_t)sizeof(T);
-    const uint32_t sstep = (uint32_t)(kRows * nx) * (uint32_t)sizeof(T);
-    const int srows = x0 + sc < nx ? ny - y0 - srow : 0;  // rows from srow on inside the volume
+    constexpr int kDrop = (int)0xfffffff0u;
+    constexpr bool kPieces = !WORDS && TXW >= 128;
+    constexpr int kLanes = WORDS ? TXW / 4 : kPieces ? TXW * (int)sizeof(T) / 8 : TXW;  // threads per row
+    constexpr int kRows = kT / kLanes, kBody = (TY + kRows - 1) / kRows;
+    constexpr int kEdge = kPieces ? (TY * 16 + kT - 1) / kT : 0;
+    constexpr int kStores = kBody + kEdge;
+    const int sj = tid % kLanes, srow = tid / kLanes;
+    const int cols = min(TXW, nx - x0);  // columns of the tile inside the volume
+    const uint32_t rowb = (uint32_t)nx * (uint32_t)sizeof(T);
+    const uint32_t sbase = (uint32_t)(y0 + srow) * rowb + (uint32_t)x0 * (uint32_t)sizeof(T);
+    const uint32_t ebase = (uint32_t)(y0 + tid / 16) * rowb + (uint32_t)x0 * (uint32_t)sizeof(T);
     T* wp = out + (size_t)z0 * plane;
     auto store_out = [&](int zo, int buf) {
+        using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
         const bool live = zo >= z0 && zo < z1;
-        const rsrc_t wr = make_rsrc(wp, live ? pbytes : 0u);
-        wp += live ? plane : 0;
+        if constexpr (WORDS) {
+            const rsrc_t wr = make_rsrc(wp, live ? pbytes : 0u);
 #pragma unroll
-        for (int i = 0; i < kStores; ++i) {
-            const T* p = &sm.outs[buf][srow + i * kRows][sc];
-            int rows = srows;
-            if constexpr (kStores > 2) asm volatile("" : "+v"(rows));  // eight offsets kept would spill
-            const uint32_t so = i * kRows < rows ? sbase + (uint32_t)i * sstep : pbytes;
-            if constexpr (!WORDS) {
-                // rows that start anywhere share cache lines with the tiles
-                // beside them: kept in L2 until those are whole (64 x 16
-                // tiles, 511 x 512 x 512 uint16, r = 3: 245 -> 200 us)
-                buffer_store<T, 0>(*p, wr, so, 0u);
-            } else if constexpr (sizeof(T) == 2) {
-                using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
-                __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(p), wr, so, 0, kStoreNT);
-            } else {
-                __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t*>(p), wr, so, 0, kStoreNT);
+            for (int i = 0; i < kBody; ++i) {
+                const int row = srow + i * kRows;
+                const T* p = &sm.outs[buf][row][4 * sj];
+                const uint32_t so = (4 * sj < cols && y0 + row < ny)
+                                        ? sbase + (uint32_t)(i * kRows) * rowb + 4u * sj * (uint32_t)sizeof(T)
+                                        : (uint32_t)kDrop;
+                if constexpr (sizeof(T) == 2)
+                    __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(p), wr, so, 0, kStoreNT);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t*>(p), wr, so, 0, kStoreNT);
+            }
+        } else {
+            const uint32_t lead = (uint32_t)(reinterpret_cast<uintptr_t>(wp) & 3);
+            const rsrc_t wr = make_rsrc(reinterpret_cast<const char*>(wp) - lead, live ? pbytes + lead : 0u);
+            const int len = cols * (int)sizeof(T);
+            // rows that start anywhere share cache lines with the tiles beside
+            // them: kept in L2 until those are whole, not streamed past it
+            // (64 x 16 tiles, 511 x 512 x 512 uint16, r = 3: 245 -> 200 us)
+            if constexpr (!kPieces) {
+#pragma unroll
+                for (int i = 0; i < kBody; ++i) {
+                    const int row = srow + i * kRows;
+                    const bool ok = sj < cols && y0 + row < ny;
+                    buffer_store<T, 0>(sm.outs[buf][row][sj], wr,
+                                       ok ? sbase + (uint32_t)(i * kRows) * rowb + lead + sj * (uint32_t)sizeof(T)
+                                          : (uint32_t)kDrop,
+                                       0u);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < (kPieces ? kBody : 0); ++i) {
+                const int row = srow + i * kRows;
+                const uint32_t at = sbase + (uint32_t)(i * kRows) * rowb + lead;
+                const int head = (int)(-at & 3u);  // bytes before the first aligned word
+                const uint32_t* p = reinterpret_cast<const uint32_t*>(&sm.outs[buf][row % TY][0]) + 2 * sj;
+                const u32x2 d = *reinterpret_cast<const u32x2*>(p);
+                const uint32_t e = p[2];
+                const u32x2 w = {__builtin_amdgcn_alignbyte(d[1], d[0], head), __builtin_amdgcn_alignbyte(e, d[1], head)};
+                const bool ok = row < TY && y0 + row < ny && head + 8 * sj + 8 <= len;
+                __builtin_amdgcn_raw_buffer_store_b64(w, wr, ok ? at + head + 8 * sj : (uint32_t)kDrop, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < kEdge; ++i) {
+                const int row = tid / 16 + i * (kT / 16), e = tid & 15;
+                const uint32_t at = ebase + (uint32_t)(i * (kT / 16)) * rowb + lead;
+                const int head = (int)(-at & 3u), eb = e * (int)sizeof(T);
+                const int pos = eb < head ? eb : (max(len - head, 0) & ~7) + eb;  // bytes from the row's start
+                const T v = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(&sm.outs[buf][row % TY][0]) +
+                                                        min(pos, TXW * (int)sizeof(T)));
+                const bool ok = row < TY && y0 + row < ny && pos < len;
+                buffer_store<T, 0>(v, wr, ok ? at + pos : (uint32_t)kDrop, 0u);
             }
         }
+        wp += live ? plane : 0;
     };
 
     // rings: Q and V hold r slices, G 2r+1 (P of the mean filter in G)
