@@ -373,7 +373,7 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
             d.nx = g.nx;
             d.ny = g.ny;
             d.nz = g.nz;
-            d.words = mean9_words_ok(d.in, d.out, g.nx) ? 1 : 0;
+            d.words = mean9_words_ok(d.in, d.out, g.nx, dtype) ? 1 : 0;
             const int nzs = depth > 0 ? (g.nz + depth - 1) / depth : std::min(nzs_want, std::max(1, g.nz / 16));
             d.zs = (g.nz + nzs - 1) / nzs;
             d.tiles_x = (g.nx + tx - 1) / tx;

@@ -13,7 +13,6 @@
 // the matrix cores, in exact arithmetic, and slides a z-window through a
 // register ring while each wavefront streams down its z-strip (mean9_tile.h).
 #include <algorithm>
-#include <climits>
 #include <vector>
 
 #include "device_common.h"
@@ -52,7 +51,7 @@ hipError_t launch_box(const T* in, T* out, Geom g, uint32_t gate, hipStream_t s)
     const int zs = default_zs(tiles_x * tiles_y, g.nz, resident_groups((const void*)kern, threads));
     const int total = tiles_x * tiles_y * ((g.nz + zs - 1) / zs);
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
-    const int words = mean9_words_ok(in, out, g.nx) ? 1 : 0;
+    const int words = mean9_words_ok(in, out, g.nx, sizeof(T) == 1 ? LNF_U8 : LNF_U16) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(total), dim3(threads), 0, s, in, out, g, zs, tiles_x, tiles_y,
                        total, gate, 1.0 / n, words, (const uint32_t*)nullptr);
     return hipGetLastError();
@@ -79,34 +78,63 @@ struct Variant {
 constexpr Variant kVariants[] = {{64, 16, 256}, {128, 32, 512}, {32, 16, 128}, {128, 16, 512}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-// Costs are kept for rows that are staged and stored as whole words (nx a
-// multiple of 4) and for others, whose stores go voxel by voxel.
 // The default tile is the variant and strip depth with the least estimated
-// time: rounds of resident workgroups x iterations of a strip x time of an
-// iteration.  Iterations come in whole blocks of 2r+2 and include the 4r
-// slices of z-halo, the two of the pipeline.  Times of an iteration (10 ns)
-// with one workgroup on a CU, and for each further one, measured on 64^3 to
-// 512^3 volumes: the wide tiles move the least halo and win where a volume has
-// a strip for every CU (512^3, r = 3, uint16: 128 x 32 123 us, 128 x 16 133,
-// 64 x 16 168, 32 x 16 248; uint8 69, 81, 106, 176); below that the narrow
-// ones do (64^3 uint16: 32 x 16 10.3 us, 64 x 16 11.4, 128 x 32 22).  The
-// 128 x 32 tile of uint16 at r = 4 spills registers and is not chosen.
+// time: for each round of resident workgroups, iterations of a strip x time of
+// an iteration.  Iterations come in whole blocks of 2r+2 and include the 4r
+// slices of z-halo, the two of the pipeline.  at[n - 1] is the measured time of
+// an iteration (10.5 ns) with n workgroups on a CU, for n up to what the
+// registers let be resident; within 5 % the same for r = 1, 2, 3 and for the
+// shapes measured (128 x 256 x 200 to 256 x 256 x 150).  It steps where a SIMD
+// gets one wavefront more: the narrow tiles, whose workgroups are two
+// wavefronts, run four to a CU in little more than the time of one.
+// Kept for rows that are staged and stored as whole words (mean9_words_ok) and
+// for others, which are shifted as they are read and stored.
 struct TileCost {
-    int one, more, resident;
+    int at[6];  // 0: not resident
 };
-constexpr TileCost kCostU16[2][kNumVariants] = {{{38, 22, 3}, {104, 0, 1}, {36, 12, 6}, {64, 0, 1}},
-                                                {{36, 20, 3}, {84, 0, 1}, {33, 12, 6}, {50, 0, 1}}};
-constexpr TileCost kCostU8[2][kNumVariants] = {{{30, 16, 4}, {62, 0, 1}, {28, 8, 8}, {44, 20, 2}},
-                                               {{28, 14, 4}, {48, 0, 1}, {26, 8, 8}, {36, 20, 2}}};
+constexpr TileCost kCostU16[2][kNumVariants] = {
+    {{{44, 61, 84, 111, 136}}, {{100}}, {{37, 51, 54, 59, 78, 85}}, {{67, 134}}},
+    {{{34, 48, 69, 92, 113}}, {{77}}, {{28, 41, 42, 47, 65, 70}}, {{46, 98}}}};
+constexpr TileCost kCostU8[2][kNumVariants] = {
+    {{{29, 38, 52, 65, 82}}, {{61}}, {{26, 33, 34, 36, 50, 61}}, {{44, 76}}},
+    {{{22, 28, 40, 51, 66}}, {{40}}, {{19, 24, 26, 28, 38, 48}}, {{30, 53}}}};
 // At r = 4 the rings take more registers, so fewer workgroups are resident.
 constexpr int kResidentU16R4[kNumVariants] = {2, 1, 4, 1}, kResidentU8R4[kNumVariants] = {3, 1, 6, 1};
 
+// whether rows start at whole words, given volumes that do
+int row_words(int dtype, int nx) { return nx % (dtype == LNF_U8 ? 4 : 2) == 0; }
+
 TileCost cost_of(int dtype, int variant, int r, Geom g)
 {
-    const int words = g.nx % 4 == 0;
+    const int words = row_words(dtype, g.nx);
     TileCost c = dtype == LNF_U8 ? kCostU8[words][variant] : kCostU16[words][variant];
-    if (r == 4) c.resident = dtype == LNF_U8 ? kResidentU8R4[variant] : kResidentU16R4[variant];
+    if (r == 4)
+        for (int n = dtype == LNF_U8 ? kResidentU8R4[variant] : kResidentU16R4[variant]; n < 6; ++n) c.at[n] = 0;
     return c;
+}
+
+int resident_of(const TileCost& c)
+{
+    int n = 1;
+    while (n < 6 && c.at[n]) ++n;
+    return n;
+}
+
+// What the halos cost once the volume does not stay in the caches: percent of
+// the time above, by variant.  A row of a narrow tile is part of a 128-byte
+// line that its neighbours fetch again.  Between 64 MB and 256 MB (input and
+// output) that shows for the 32-wide tile (320^3 uint8, r = 3: 64 x 16 25.6 us,
+// 32 x 16 29.2), beyond it is memory that bounds the narrow tiles (512^3 uint16,
+// r = 3: 128 x 32 129 us, 128 x 16 148, 64 x 16 172, 32 x 16 250).
+constexpr int kMidU16[kNumVariants] = {100, 100, 120, 100}, kMidU8[kNumVariants] = {100, 100, 140, 100};
+constexpr int kLarge[kNumVariants] = {125, 100, 190, 112};
+
+int traffic_percent(int dtype, int variant, double voxels)
+{
+    const double bytes = voxels * (dtype == LNF_U8 ? 2 : 4);
+    if (bytes > 268435456.0) return kLarge[variant];
+    if (bytes > 67108864.0) return dtype == LNF_U8 ? kMidU8[variant] : kMidU16[variant];
+    return 100;
 }
 
 long long tile_groups(int variant, int zs, Geom g)
@@ -132,26 +160,29 @@ bool tile_eligible(int variant, int want, int dtype, int r)
 TileCfg resolve_tile(TileCfg want, int dtype, int r, Geom g)
 {
     TileCfg best = want;
-    int best_cost = INT_MAX;
+    double best_cost = -1;
     const int cus = device_cus(), most = std::max(1, g.nz / 4);  // strips of 4 slices at least
     for (int v = 0; v < kNumVariants; ++v) {
         if (!tile_eligible(v, want.variant, dtype, r)) continue;
         const TileCost c = cost_of(dtype, v, r, g);
+        const int resident = resident_of(c), percent = traffic_percent(dtype, v, (double)g.nx * g.ny * g.nz);
         const int cols = (int)std::min<long long>(tile_groups(v, g.nz, g), 1 << 24);
         // strip counts that fill whole rounds: one round of 1 .. resident
         // workgroups per CU, or up to four full ones
-        for (int i = 1; i < c.resident + 4; ++i) {
-            const int per_cu = std::min(i, c.resident), rounds = i - per_cu + 1;
+        for (int i = 1; i < resident + 4; ++i) {
+            const int per_cu = std::min(i, resident), rounds = i - per_cu + 1;
             int nzs = want.zs > 0 ? (g.nz + want.zs - 1) / want.zs
                                   : std::min(most, std::max(1, cus * per_cu * rounds / cols));
             const int zs = want.zs > 0 ? want.zs : (g.nz + nzs - 1) / nzs;
             nzs = (g.nz + zs - 1) / zs;
             const int groups = (int)std::min<long long>((long long)cols * nzs, 1 << 30);
-            const int n = std::min(c.resident, (groups + cus - 1) / cus);
-            const double cost = (double)((groups + cus * n - 1) / (cus * n)) * tile_iterations(zs, r) *
-                                (c.one + (n - 1) * c.more);
-            if (cost < best_cost) {
-                best_cost = (int)std::min(cost, 2e9);
+            const int n = (groups + cus - 1) / cus;  // workgroups of a CU
+            const int time = n / resident * c.at[resident - 1] + (n % resident ? c.at[n % resident - 1] : 0);
+            // a further round starts with its weights and first slices: 3 iterations
+            const double cost =
+                ((double)time * tile_iterations(zs, r) + (n - 1) / resident * 3 * c.at[resident - 1]) * percent;
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
                 best = TileCfg{v, zs};
             }
         }
@@ -169,7 +200,7 @@ hipError_t launch_stream(const T* in, T* out, Geom g, uint32_t gate, int zs, hip
     const int nzs = (g.nz + zs - 1) / zs;
     const int total = tiles_x * tiles_y * nzs;
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
-    const int words = mean9_words_ok(in, out, g.nx) ? 1 : 0;
+    const int words = mean9_words_ok(in, out, g.nx, sizeof(T) == 1 ? LNF_U8 : LNF_U16) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(total), dim3(threads), 0, s, in, out, g, zs, tiles_x, tiles_y,
                        total, gate, 1.0 / (9.0 * n), words, gate_dev);
     return hipGetLastError();
@@ -221,6 +252,20 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
 
 int mean9_variants() { return kNumVariants; }
 
+// The tile and strip depth of a batch class: work spread over the CUs and a
+// tail of the longest strip.  Each volume pushes the others out of the caches,
+// which costs the narrow tiles more than alone (64 volumes of 64^3 to 384^3:
+// 902 us with these times of an iteration, 1045 us with those of single calls,
+// which prefer 32 x 16): {with one workgroup on a CU, more for each further
+// one, resident}.
+struct BatchCost {
+    int one, more, resident;
+};
+constexpr BatchCost kBatchU16[2][kNumVariants] = {{{38, 22, 3}, {104, 0, 1}, {36, 12, 6}, {64, 0, 1}},
+                                                  {{36, 20, 3}, {84, 0, 1}, {33, 12, 6}, {50, 0, 1}}};
+constexpr BatchCost kBatchU8[2][kNumVariants] = {{{30, 10, 4}, {62, 0, 1}, {28, 8, 8}, {44, 20, 2}},
+                                                 {{28, 9, 4}, {48, 0, 1}, {26, 8, 8}, {36, 20, 2}}};
+
 TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>& g)
 {
     constexpr int kDepths[] = {16, 24, 32, 48, 64, 96, 128, 192};
@@ -231,9 +276,11 @@ TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>&
         if (!tile_eligible(v, variant, dtype, r)) continue;
         float work[8] = {}, longest[8] = {};
         for (const Geom& q : g) {
-            const TileCost c = cost_of(dtype, v, r, q);
-            const float tau = (float)(c.one + (c.resident - 1) * c.more);
-            const float cols = (float)tile_groups(v, q.nz, q) * tau / c.resident;
+            const int words = row_words(dtype, q.nx);
+            const BatchCost c = dtype == LNF_U8 ? kBatchU8[words][v] : kBatchU16[words][v];
+            const int resident = r == 4 ? (dtype == LNF_U8 ? kResidentU8R4 : kResidentU16R4)[v] : c.resident;
+            const float tau = (float)(c.one + (resident - 1) * c.more);
+            const float cols = (float)tile_groups(v, q.nz, q) * tau / resident;
             for (int i = 0; i < 8; ++i) {
                 const int nzs = (q.nz + kDepths[i] - 1) / kDepths[i];
                 const float iters = (float)tile_iterations((q.nz + nzs - 1) / nzs, r);
@@ -242,7 +289,7 @@ TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>&
             }
         }
         for (int i = 0; i < 8; ++i) {
-            const float cost = work[i] / cus + longest[i];  // and a tail of the longest strip
+            const float cost = work[i] / cus + longest[i];
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = TileCfg{v, kDepths[i]};

@@ -256,64 +256,84 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
     const uint32_t sbase = (uint32_t)(y0 + srow) * rowb + (uint32_t)x0 * (uint32_t)sizeof(T);
     const uint32_t ebase = (uint32_t)(y0 + tid / 16) * rowb + (uint32_t)x0 * (uint32_t)sizeof(T);
     T* wp = out + (size_t)z0 * plane;
-    auto store_out = [&](int zo, int buf) {
-        using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
-        const bool live = zo >= z0 && zo < z1;
-        if constexpr (WORDS) {
-            const rsrc_t wr = make_rsrc(wp, live ? pbytes : 0u);
+    // held: what a thread stores, read from LDS before the y-pass and stored
+    // behind it
+    using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
+    using body_t = std::conditional_t<kPieces || (WORDS && sizeof(T) == 2), u32x2, std::conditional_t<WORDS, uint32_t, T>>;
+    body_t held[kBody];
+    T ends[kEdge ? kEdge : 1];
+    // bytes of the row at `at` before its first aligned word; the voxel of a
+    // row's ends that this thread stores, in bytes from the row's start
+    auto head_of = [](uint32_t at) { return (int)(-at & 3u); };
+    auto end_pos = [&](int head) {
+        const int eb = (tid & 15) * (int)sizeof(T);
+        return eb < head ? eb : (max(cols * (int)sizeof(T) - head, 0) & ~7) + eb;
+    };
+    const int scol = WORDS ? min(4 * sj, max(cols - 4, 0)) : sj;
+    uint32_t so[kBody];  // not kPieces: the offsets stored to
 #pragma unroll
-            for (int i = 0; i < kBody; ++i) {
-                const int row = srow + i * kRows;
-                const T* p = &sm.outs[buf][row][4 * sj];
-                const uint32_t so = (4 * sj < cols && y0 + row < ny)
-                                        ? sbase + (uint32_t)(i * kRows) * rowb + 4u * sj * (uint32_t)sizeof(T)
-                                        : (uint32_t)kDrop;
-                if constexpr (sizeof(T) == 2)
-                    __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(p), wr, so, 0, kStoreNT);
-                else
-                    __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t*>(p), wr, so, 0, kStoreNT);
-            }
-        } else {
-            const uint32_t lead = (uint32_t)(reinterpret_cast<uintptr_t>(wp) & 3);
-            const rsrc_t wr = make_rsrc(reinterpret_cast<const char*>(wp) - lead, live ? pbytes + lead : 0u);
-            const int len = cols * (int)sizeof(T);
-            // rows that start anywhere share cache lines with the tiles beside
-            // them: kept in L2 until those are whole, not streamed past it
-            // (64 x 16 tiles, 511 x 512 x 512 uint16, r = 3: 245 -> 200 us)
-            if constexpr (!kPieces) {
+    for (int i = 0; i < kBody; ++i) {
+        constexpr int kPer = WORDS ? 4 : 1;
+        so[i] = (kPer * sj < cols && y0 + srow + i * kRows < ny)
+                    ? sbase + (uint32_t)(i * kRows) * rowb + (uint32_t)scol * (uint32_t)sizeof(T)
+                    : (uint32_t)kDrop;
+    }
+    auto read_out = [&](int buf) {
+        const uint32_t lead = (uint32_t)(reinterpret_cast<uintptr_t>(wp) & 3);
 #pragma unroll
-                for (int i = 0; i < kBody; ++i) {
-                    const int row = srow + i * kRows;
-                    const bool ok = sj < cols && y0 + row < ny;
-                    buffer_store<T, 0>(sm.outs[buf][row][sj], wr,
-                                       ok ? sbase + (uint32_t)(i * kRows) * rowb + lead + sj * (uint32_t)sizeof(T)
-                                          : (uint32_t)kDrop,
-                                       0u);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < (kPieces ? kBody : 0); ++i) {
-                const int row = srow + i * kRows;
-                const uint32_t at = sbase + (uint32_t)(i * kRows) * rowb + lead;
-                const int head = (int)(-at & 3u);  // bytes before the first aligned word
+        for (int i = 0; i < kBody; ++i) {
+            const int row = srow + i * kRows;
+            if constexpr (WORDS) {
+                using at4_t = body_t __attribute__((aligned(4)));
+                held[i] = *reinterpret_cast<const at4_t*>(&sm.outs[buf][row][scol]);
+            } else if constexpr (kPieces) {
+                const int head = head_of(sbase + (uint32_t)(i * kRows) * rowb + lead);
                 const uint32_t* p = reinterpret_cast<const uint32_t*>(&sm.outs[buf][row % TY][0]) + 2 * sj;
                 const u32x2 d = *reinterpret_cast<const u32x2*>(p);
-                const uint32_t e = p[2];
-                const u32x2 w = {__builtin_amdgcn_alignbyte(d[1], d[0], head), __builtin_amdgcn_alignbyte(e, d[1], head)};
-                const bool ok = row < TY && y0 + row < ny && head + 8 * sj + 8 <= len;
-                __builtin_amdgcn_raw_buffer_store_b64(w, wr, ok ? at + head + 8 * sj : (uint32_t)kDrop, 0, 0);
+                held[i] = u32x2{__builtin_amdgcn_alignbyte(d[1], d[0], head), __builtin_amdgcn_alignbyte(p[2], d[1], head)};
+            } else {
+                held[i] = sm.outs[buf][row][sj];
             }
+        }
 #pragma unroll
-            for (int i = 0; i < kEdge; ++i) {
-                const int row = tid / 16 + i * (kT / 16), e = tid & 15;
-                const uint32_t at = ebase + (uint32_t)(i * (kT / 16)) * rowb + lead;
-                const int head = (int)(-at & 3u), eb = e * (int)sizeof(T);
-                const int pos = eb < head ? eb : (max(len - head, 0) & ~7) + eb;  // bytes from the row's start
-                const T v = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(&sm.outs[buf][row % TY][0]) +
-                                                        min(pos, TXW * (int)sizeof(T)));
-                const bool ok = row < TY && y0 + row < ny && pos < len;
-                buffer_store<T, 0>(v, wr, ok ? at + pos : (uint32_t)kDrop, 0u);
+        for (int i = 0; i < kEdge; ++i) {
+            const int row = tid / 16 + i * (kT / 16);
+            const int pos = end_pos(head_of(ebase + (uint32_t)(i * (kT / 16)) * rowb + lead));
+            ends[i] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(&sm.outs[buf][row % TY][0]) +
+                                                  min(pos, TXW * (int)sizeof(T)));
+        }
+    };
+    auto store_out = [&](int zo) {
+        const bool live = zo >= z0 && zo < z1;
+        // rows that start anywhere share cache lines with the tiles beside
+        // them: kept in L2 until those are whole, not streamed past it
+        // (64 x 16 tiles, 511 x 512 x 512 uint16, r = 3: 245 -> 200 us)
+        const uint32_t lead = kPieces ? (uint32_t)(reinterpret_cast<uintptr_t>(wp) & 3) : 0u;
+        const rsrc_t wr = make_rsrc(reinterpret_cast<const char*>(wp) - lead, live ? pbytes + lead : 0u);
+#pragma unroll
+        for (int i = 0; i < kBody; ++i) {
+            const int row = srow + i * kRows;
+            const uint32_t at = sbase + (uint32_t)(i * kRows) * rowb + lead;
+            if constexpr (WORDS) {
+                if constexpr (sizeof(T) == 2)
+                    __builtin_amdgcn_raw_buffer_store_b64(held[i], wr, so[i], 0, kStoreNT);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b32(held[i], wr, so[i], 0, kStoreNT);
+            } else if constexpr (kPieces) {
+                const int from = head_of(at) + 8 * sj;
+                const bool ok = row < TY && y0 + row < ny && from + 8 <= cols * (int)sizeof(T);
+                __builtin_amdgcn_raw_buffer_store_b64(held[i], wr, ok ? at + from : (uint32_t)kDrop, 0, 0);
+            } else {
+                buffer_store<T, 0>(held[i], wr, so[i], 0u);
             }
+        }
+#pragma unroll
+        for (int i = 0; i < kEdge; ++i) {
+            const int row = tid / 16 + i * (kT / 16);
+            const uint32_t at = ebase + (uint32_t)(i * (kT / 16)) * rowb + lead;
+            const int pos = end_pos(head_of(at));
+            const bool ok = row < TY && y0 + row < ny && pos < cols * (int)sizeof(T);
+            buffer_store<T, 0>(ends[i], wr, ok ? at + pos : (uint32_t)kDrop, 0u);
         }
         wp += live ? plane : 0;
     };
@@ -331,13 +351,13 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
 
     const int ns = (z1 - z0) + LAG;  // input slices z0 - ZH .. z1 - 1 + ZH
     // vector-memory operations younger than a slice's staging when it is waited for
-    constexpr int kWait = (PF - 1) * (NLOAD + kStores);
-    // each slice but the first after dropped stores: the operations of an iteration
-    stage(0);
+    constexpr int kWait = (PF - 1) * (NLOAD + kStores) + kStores;
+    // each slice before dropped stores: the operations of an iteration
+    read_out(0);
 #pragma unroll
-    for (int p = 1; p < PF; ++p) {
-        store_out(-1, 0);
+    for (int p = 0; p < PF; ++p) {
         stage(p);
+        store_out(-1);
     }
     wait_vmem_le<kWait>();
     barrier_lds();
@@ -358,7 +378,7 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
             const int buf = u & 1;  // == k & 1 because D is even
             // outputs of iteration k-1
             const int zo = z0 + k - 2 - LAG;
-            store_out(zo, buf ^ 1);
+            read_out(buf ^ 1);
             stage((u + PF) % NRB);  // slice k+PF; the buffer held slice k-1
 #pragma unroll
             for (int o = 0; o < NO; ++o) {
@@ -414,6 +434,7 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
                 }
                 *reinterpret_cast<out_t*>(&sm.outs[buf][16 * o + l][16 * wave + 4 * gq]) = w;
             }
+            store_out(zo);
             // x-pass of every raw block, rounded to f16 (exact)
 #pragma unroll
             for (int rt = 0; rt < NR; ++rt) {
@@ -453,7 +474,7 @@ __device__ __forceinline__ void mean9_tile(M9Smem<R, TY, TXW, T>& sm, bool words
                                            int x0, int y0, int z0, int z1, uint32_t gate,
                                            double inv_div, int tid)
 {
-    if (words)
+    if (words && g.nx - x0 >= 4)
         mean9_body<R, TY, T, GATE, TXW, BOX, true>(sm, in, out, g, x0, y0, z0, z1, gate, inv_div, tid);
     else
         mean9_body<R, TY, T, GATE, TXW, BOX, false>(sm, in, out, g, x0, y0, z0, z1, gate, inv_div, tid);

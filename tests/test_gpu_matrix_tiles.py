@@ -70,6 +70,26 @@ def test_tile_edges_every_variant_and_alignment(dt, r):
     f.close()
 
 
+@pytest.mark.parametrize("nx", [2, 4, 6, 30, 34, 62, 66, 126, 130, 134, 258])
+@pytest.mark.parametrize("r", [1, 3, 4])
+def test_even_rows_of_uint16_start_at_words(r, nx):
+    """nx mod 4 == 2: the last four outputs of a row overlap the ones before
+    them, a tile with two columns left goes the other way; guard bytes stay."""
+    from paper_1807_03119_amd.api import Filter
+    f = Filter(_lib.LNF_MEAN9, 0)
+    vol = _values((nx, 18, 5), np.uint16, "uniform", 40 + nx)
+    want = oracle.filter_volume(vol, r)
+    dev = _at_offset(vol, torch.uint16, 2)
+    buf = torch.full((vol.size + 128,), 0xA5A5 - 65536, dtype=torch.int16, device="cuda")
+    out = buf[64:64 + vol.size].view(torch.uint16).view(vol.shape)
+    for variant in range(-1, _lib.lnf_tile_variants(_lib.LNF_MEAN9, _lib.LNF_U16, r)):
+        f(dev, r, out=out, variant=variant)
+        assert np.array_equal(out.cpu().numpy(), want), variant
+    guard = torch.cat([buf[:64], buf[64 + vol.size:]]).cpu()
+    assert bool((guard == 0xA5A5 - 65536).all())
+    f.close()
+
+
 def test_stores_stay_inside_the_volume():
     """No byte before or after an output of odd rows changes."""
     from paper_1807_03119_amd.api import Filter
