@@ -604,7 +604,7 @@ def main():
         ms2, _ = time_launches(lambda: g.filter_otsu(vol, args.radius, out=out), 5, 1, stream)
         extras["otsu"].update({"threshold": int(t_otsu), "pipeline_ms": ms2,
                                "pipeline_Gvox_s": nvox / (ms2 * 1e-3) / 1e9,
-                               "pipeline": "histogram, exact Otsu on the host, gated MEAN9 "
+                               "pipeline": "histogram, exact Otsu, gated MEAN9 "
                                            f"r={args.radius}"})
         g.close()
         gen = torch.Generator(device="cuda").manual_seed(SEED + 1)

@@ -18,7 +18,8 @@
 // Per call: one H2D copy of the job table (from one of four pinned staging
 // slots, queue counters uploaded as zero, so the call can be captured in a
 // graph without memset nodes) and one launch per non-empty class, all on the
-// caller's stream.
+// caller's stream.  A MEAN9 volume whose planes the tile does not address
+// (mean9_plane_ok) is launched singly.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -255,7 +255,7 @@ int mean9_variants() { return kNumVariants; }
 // The tile and strip depth of a batch class: work spread over the CUs and a
 // tail of the longest strip.  Each volume pushes the others out of the caches,
 // which costs the narrow tiles more than alone (64 volumes of 64^3 to 384^3:
-// 902 us with these times of an iteration, 1045 us with those of single calls,
+// 857 us with these times of an iteration, 1049 us with those of single calls,
 // which prefer 32 x 16): {with one workgroup on a CU, more for each further
 // one, resident}.
 struct BatchCost {
