@@ -198,3 +198,29 @@ def test_otsu_calls_in_flight_on_several_streams():
         assert t == ootsu.otsu_threshold(np.bincount(v.ravel(), minlength=65536))
         assert np.array_equal(o.cpu().numpy(), oracle.filter_volume(v, 2, oracle.MEAN9, t))
     f.close()
+
+
+@pytest.mark.parametrize("lead", range(8))
+@pytest.mark.parametrize("n", [1, 7, 8, 15, 16385, 65537])
+def test_histogram_of_volumes_that_start_anywhere(n, lead):
+    """Voxels before the first 16-byte vector, the vectors, and what is left."""
+    from paper_1807_03119_amd.api import Filter
+    vol = _values((n, 1, 1), np.uint16, "uniform", 60 + n)
+    with Filter(_lib.LNF_MEAN9, 0) as f:
+        got = f.histogram(_at_offset(vol, torch.uint16, lead)).cpu().numpy()
+    assert np.array_equal(got, np.bincount(vol.ravel(), minlength=65536))
+
+
+@pytest.mark.parametrize("value", [0, 1, 65534, 65535])
+def test_histogram_counts_do_not_carry_between_the_halves_of_a_word(value):
+    """One value over several chunks of every workgroup, ends on both sides."""
+    from paper_1807_03119_amd.api import Filter
+    n = 40_000_013
+    buf = torch.zeros(n + 16, dtype=torch.int16, device="cuda")
+    buf.fill_(value if value < 32768 else value - 65536)
+    vol = buf[3:3 + n].view(torch.uint16).view(1, 1, n)
+    with Filter(_lib.LNF_MEAN9, 0) as f:
+        got = f.histogram(vol).cpu()
+    want = torch.zeros(65536, dtype=torch.int64)
+    want[value] = n
+    assert torch.equal(got, want)
