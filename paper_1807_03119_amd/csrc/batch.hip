@@ -18,8 +18,7 @@
 // Per call: one H2D copy of the job table (from one of four pinned staging
 // slots, queue counters uploaded as zero, so the call can be captured in a
 // graph without memset nodes) and one launch per non-empty class, all on the
-// caller's stream.  A MEAN9 volume whose planes the tile does not address
-// (mean9_plane_ok) is launched singly.
+// caller's stream.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -296,16 +295,8 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
     BatchSlot& s = *sp;
 
     // order: by class, then larger jobs first (their tiles get the low indices)
-    std::vector<int> order;
-    for (int i = 0; i < n; ++i) {
-        if (h->rule != LNF_MEAN9 || h->geom || mean9_plane_ok(jobs[i].dtype, geoms[i])) {
-            order.push_back(i);
-        } else if (launch_rule(h->rule, h->geom, jobs[i].in, jobs[i].out, jobs[i].dtype, jobs[i].radius,
-                               geoms[i], h->gate, TileCfg{-1, 0}, stream) != hipSuccess) {
-            return LNF_EHIP;
-        }
-    }
-    n = (int)order.size();
+    std::vector<int> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
     auto vox = [&](int i) { return (double)geoms[i].nx * geoms[i].ny * geoms[i].nz; };
     std::sort(order.begin(), order.end(), [&](int a, int b) {
         const int ca = batch_class(jobs[a].radius, jobs[a].dtype);

@@ -46,14 +46,6 @@ inline bool mean9_words_ok(const void* in, const void* out, int nx, int dtype)
            (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 4 == 0;
 }
 
-// The tile ends a slice at a whole word, which a plane within 16 bytes of 4 GiB
-// (uint16, nx * ny >= 2^31 - 8) leaves no room for: such a volume runs on the
-// geometry kernel, which gives the same bytes.
-inline bool mean9_plane_ok(int dtype, Geom g)
-{
-    return dtype == LNF_U8 || (int64_t)g.nx * g.ny < (1ll << 31) - 8;
-}
-
 // ---- geometry variants (plane_tile.h): LNF_GEOM_* bits, both rules ---------
 hipError_t launch_geometry(int rule, uint32_t geom, const void* in, void* out, int dtype, int r,
                            Geom g, uint32_t gate, int zs, hipStream_t s, TileCfg* plan = nullptr,

@@ -316,9 +316,6 @@ hipError_t launch_box_mean(const void* in, void* out, int dtype, int r, Geom g, 
 hipError_t launch_mean9(const void* in, void* out, int dtype, int r, Geom g, uint32_t gate,
                         TileCfg cfg, hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
-    if (!plan && !mean9_plane_ok(dtype, g))
-        return launch_geometry(LNF_MEAN9, 0, in, out, dtype, r, g, gate, cfg.zs, s, nullptr,
-                               gate_dev);
     if (dtype == LNF_U8) return dispatch_r<uint8_t>(in, out, r, g, gate, cfg, s, plan, gate_dev);
     return dispatch_r<uint16_t>(in, out, r, g, gate, cfg, s, plan, gate_dev);
 }

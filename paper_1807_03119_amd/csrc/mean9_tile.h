@@ -131,23 +131,30 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
 
     // ---- staging: slot tid + i * kT of a buffer holds chunk slot % NC of row
     // slot / NC; lanes past the tile repeat the last slot's.  off: its byte
-    // offset in a slice; only chunks outside the volume start before the slice,
-    // and they are moved to its start.
+    // offset from the first staged voxel of the slice (row ys, column xs); only
+    // chunks outside the volume start before that, and they are moved to it.
+    // Addresses count from the tile's first voxel and end behind its last row,
+    // so that they, the drop offset below included, fit 32 bits for planes of
+    // up to 4 GiB.
     const int xl = x0 - CV;  // first staged column
+    const int xs = max(xl, 0), ys = max(y0 - 2 * R, 0);
+    const int yn = min(y0 - 2 * R + S::LY, ny) - ys;  // staged rows inside the volume
+    const size_t sorigin = (size_t)ys * nx + xs;
+    const uint32_t sbytes = (uint32_t)(min((int64_t)(plane - sorigin), (int64_t)(yn - 1) * nx + NC * CV) * (int)sizeof(T));
     uint32_t off[NLOAD];
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
         const int e = min(tid + i * kT, S::NCH - 1);
         const int row = e / NC, c = e - row * NC;
-        const int64_t at = (int64_t)clampi(y0 - 2 * R + row, 0, ny - 1) * nx + xl + CV * c;
+        const int64_t at = (int64_t)(clampi(y0 - 2 * R + row, 0, ny - 1) - ys) * nx + xl - xs + CV * c;
         off[i] = (uint32_t)(max(at, (int64_t)0) * (int)sizeof(T));
     }
     // the next slice to load, clamped into the volume
     int zl = z0 - ZH;
-    const T* lp = in + (size_t)clampi(zl, 0, g.nz - 1) * plane;
+    const T* lp = in + (size_t)clampi(zl, 0, g.nz - 1) * plane + sorigin;
     auto stage = [&](int buf) {  // the next slice into buffer buf
         const uint32_t lead = WORDS ? 0u : (uint32_t)(reinterpret_cast<uintptr_t>(lp) & 3);
-        const rsrc_t rs = make_rsrc(reinterpret_cast<const char*>(lp) - lead, WORDS ? pbytes : (min(pbytes, 0xfffffff8u) + lead + 3) & ~3u);
+        const rsrc_t rs = make_rsrc(reinterpret_cast<const char*>(lp) - lead, WORDS ? sbytes : (sbytes + lead + 3) & ~3u);
 #pragma unroll
         for (int i = 0; i < NLOAD; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -199,12 +206,12 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
     // ---- A operands: raw row block rt holds rows y0 - 8 + 16 rt + l, staged
     // from y0 - 2R on; rows outside have no weight and read a staged one
     int aoff[NR];       // byte offset in a buffer
-    uint32_t arow[NR];  // byte offset of the staged row in its slice (modulo 4)
+    uint32_t arow[NR];  // byte offset of the staged row, as off (modulo 4)
 #pragma unroll
     for (int rt = 0; rt < NR; ++rt) {
         const int row = clampi(16 * rt + l - 8 + 2 * R, 0, S::LY - 1);
         aoff[rt] = row * NC * 16 + (CV - 8 + 8 * (2 * wave + gq)) * (int)sizeof(T);
-        arow[rt] = ((uint32_t)clampi(y0 - 2 * R + row, 0, ny - 1) * (uint32_t)nx + (uint32_t)xl) * (uint32_t)sizeof(T);
+        arow[rt] = ((uint32_t)(clampi(y0 - 2 * R + row, 0, ny - 1) - ys) * (uint32_t)nx + (uint32_t)(xl - xs)) * (uint32_t)sizeof(T);
     }
     // the slice read, clamped as staged, and its bytes past an aligned word
     int zr = z0 - ZH;
@@ -244,7 +251,9 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
     // threads to a row (511 x 512 x 512 uint16, r = 3, 128 x 32 tiles: 175 -> 156
     // us against voxel by voxel); narrower tiles, whose rows have more ends,
     // store voxel by voxel (64 x 16: 200 us against 228).
-    // Outputs outside the volume get an offset past its end, and slices that
+    // Outputs outside the volume get an offset past the tile's end (the bytes from
+    // a tile's first voxel to its last stay 16 below 4 GiB: of its last row it has
+    // 256 bytes at most, of a plane below 4 GiB all of it), and slices that
     // are not the strip's an empty buffer resource: either is dropped by the
     // range check, so every iteration issues the same memory operations and
     // its waits can leave the younger ones in flight.
@@ -257,9 +266,9 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
     const int sj = tid % kLanes, srow = tid / kLanes;
     const int cols = min(TXW, nx - x0);  // columns of the tile inside the volume
     const uint32_t rowb = (uint32_t)nx * (uint32_t)sizeof(T);
-    const uint32_t sbase = (uint32_t)(y0 + srow) * rowb + (uint32_t)x0 * (uint32_t)sizeof(T);
-    const uint32_t ebase = (uint32_t)(y0 + tid / 16) * rowb + (uint32_t)x0 * (uint32_t)sizeof(T);
-    T* wp = out + (size_t)z0 * plane;
+    const uint32_t sbase = (uint32_t)srow * rowb, ebase = (uint32_t)(tid / 16) * rowb;
+    const uint32_t tbytes = (uint32_t)(((int64_t)(min(TY, ny - y0) - 1) * nx + cols) * (int)sizeof(T));
+    T* wp = out + (size_t)z0 * plane + (size_t)y0 * nx + x0;
     // held: what a thread stores, read from LDS before the y-pass and stored
     // behind it, so that the read's latency is covered (the same tiles: 23.1 ->
     // 22.1 us; 511 x 512 x 512, r = 3, 128 x 32: 152 -> 149)
@@ -316,7 +325,7 @@ __device__ __forceinline__ void mean9_body(M9Smem<R, TY, TXW, T>& sm, const T* _
         // them: kept in L2 until those are whole, not streamed past it
         // (64 x 16 tiles, 511 x 512 x 512 uint16, r = 3: 245 -> 200 us)
         const uint32_t lead = kPieces ? (uint32_t)(reinterpret_cast<uintptr_t>(wp) & 3) : 0u;
-        const rsrc_t wr = make_rsrc(reinterpret_cast<const char*>(wp) - lead, live ? pbytes + lead : 0u);
+        const rsrc_t wr = make_rsrc(reinterpret_cast<const char*>(wp) - lead, live ? tbytes + lead : 0u);
 #pragma unroll
         for (int i = 0; i < kBody; ++i) {
             const int row = srow + i * kRows;

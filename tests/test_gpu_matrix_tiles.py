@@ -224,3 +224,54 @@ def test_histogram_counts_do_not_carry_between_the_halves_of_a_word(value):
     want = torch.zeros(65536, dtype=torch.int64)
     want[value] = n
     assert torch.equal(got, want)
+
+
+# ---- planes just below 4 GiB ---------------------------------------------------
+
+def _mean_at(vol, r, pts):
+    """The mean filter at listed voxels, from its definition."""
+    nz, ny, nx = vol.shape
+    off = np.arange(-r, r + 1)
+    x, y, z = (np.clip(pts[:, k, None] + off, 0, n - 1) for k, n in enumerate((nx, ny, nz)))
+    cube = vol[z[:, :, None, None], y[:, None, :, None], x[:, None, None, :]].astype(np.int64)
+    n = (2 * r + 1) ** 3
+    return ((2 * cube.sum((1, 2, 3)) + n) // (2 * n)).astype(np.uint32)
+
+
+@pytest.mark.parametrize("dims,r", [((65534, 32769, 1), 1),     # 2^32 - 4 bytes, rows are whole words
+                                    ((42966, 49981, 1), 3),     # 2^32 - 4 bytes, nx mod 4 == 2
+                                    ((2699, 795659, 1), 4),     # 2^32 - 14 bytes, odd rows
+                                    ((22605091, 95, 1), 2)])    # 2^32 - 6 bytes, few long rows
+def test_uint16_planes_up_to_four_gigabytes(dims, r):
+    """Planes whose last voxels lie within a few bytes of 4 GiB: the values at
+    random voxels, at all four edges and in the last voxels of the plane, for
+    MEAN9 alone and in a batch and for the mean filter."""
+    from paper_1807_03119_amd.api import Filter
+    nx, ny, nz = dims
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    dev = torch.empty((nz, ny, nx), dtype=torch.int16, device="cuda").random_(-32768, 32768, generator=gen)
+    host = dev.cpu().numpy().view(np.uint16)
+    rng = np.random.default_rng(17)
+    ex = np.array([0, 1, nx // 2, nx - 2, nx - 1])
+    ey = np.array([0, 1, ny // 2, ny - 2, ny - 1])
+    last = np.arange(nx * ny - 600, nx * ny)
+    pts = np.concatenate([
+        np.stack([rng.integers(0, nx, 2000), rng.integers(0, ny, 2000)], 1),
+        np.stack([ex[rng.integers(0, 5, 600)], rng.integers(0, ny, 600)], 1),
+        np.stack([rng.integers(0, nx, 600), ey[rng.integers(0, 5, 600)]], 1),
+        np.stack([last % nx, last // nx], 1)])
+    pts = np.concatenate([pts, np.zeros((len(pts), 1), pts.dtype)], 1)
+    at = torch.from_numpy(pts[:, 1].astype(np.int64) * nx + pts[:, 0]).cuda()
+    out = torch.empty_like(dev)
+
+    def taken():
+        return out.view(-1)[at].cpu().numpy().view(np.uint16).astype(np.uint32)
+    vol, res = dev.view(torch.uint16), out.view(torch.uint16)
+    want, want_mean = oracle.filter_points(host, r, pts, oracle.MEAN9), _mean_at(host, r, pts)
+    with Filter(_lib.LNF_MEAN9, 0) as f:
+        for name, call, w in (("filter", lambda: f(vol, r, out=res), want),
+                              ("batch", lambda: f.batch([(vol, res, r)]), want),
+                              ("mean", lambda: f.mean(vol, r, out=res), want_mean)):
+            out.fill_(0)
+            call()
+            assert np.array_equal(taken(), w), (dims, r, name)
