@@ -8,8 +8,9 @@
 // read the same cache lines in one instruction).  The nine clusters cover the
 // (4r+1)^3 block around the point (coordinates clamped into the volume); the
 // sixteen lanes split its (4r+1)^2 x-rows.  A row is read as the r * sizeof(T)
-// + 1 aligned words that hold its 4r+1 voxels, for every alignment, and
-// shifted into place; rows that leave the volume in x are read voxel by voxel.
+// + 1 aligned words that hold its 4r+1 voxels, for every alignment of a voxel,
+// and shifted into place; rows that leave the volume in x, and uint16 volumes
+// at an odd address, are read voxel by voxel.
 // MEAN9 needs two weighted sums of a row, S = sum_rows c(dy) c(dz) sum_x c(dx) v
 // + sum_{|dy|,|dz| <= r} sum_{|dx| <= r} v with c = 1, and 2 at 0: integer dot
 // products of the packed words with constant weights.  MINVAR9 sums each row
@@ -93,7 +94,10 @@ __global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
     const bool inside = px >= 0 && py >= 0 && pz >= 0 && px < g.nx && py < g.ny && pz < g.nz;
     if (!inside) px = py = pz = 0;
     const size_t nx = g.nx, plane = (size_t)g.nx * g.ny;
-    const bool whole = px >= 2 * R && px + 2 * R < g.nx;  // rows inside the volume in x
+    // rows inside the volume in x; a uint16 row that starts at an odd byte could
+    // end a byte past its words
+    const bool whole = px >= 2 * R && px + 2 * R < g.nx &&
+                       reinterpret_cast<uintptr_t>(in) % sizeof(T) == 0;
 
     uint32_t s[9];
     Q q[9];

@@ -135,6 +135,28 @@ def test_points_at_faces_and_alignments(dt, r):
             f.close()
 
 
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+def test_points_of_a_uint16_volume_at_an_odd_address(r):
+    """The C interface takes any byte address; a row's last voxel may then end
+    past the words that hold a row of an even address."""
+    vol = _values((4 * r + 9, 7, 6), np.uint16, "uniform", 7200 + r)
+    nz, ny, nx = vol.shape
+    pts = np.stack(np.meshgrid(np.arange(nx), [0, 3, ny - 1], [0, 2, nz - 1], indexing="ij"), -1).reshape(-1, 3)
+    xyz = torch.from_numpy(pts.astype(np.int32)).cuda()
+    out = torch.empty(len(pts), dtype=torch.int32, device="cuda")
+    buf = torch.zeros(2 * vol.size + 64, dtype=torch.uint8, device="cuda")
+    for rule, orule in ((_lib.LNF_MEAN9, oracle.MEAN9), (_lib.LNF_MINVAR9, oracle.MINVAR9)):
+        want = oracle.filter_points(vol, r, pts, orule)
+        h = _lib.lnf_create(rule, 0, 0)
+        for lead in (1, 3):
+            buf[lead:lead + 2 * vol.size].copy_(torch.from_numpy(vol.reshape(-1).view(np.uint8)).cuda())
+            rc = _lib.lnf_filter_points(h, buf.data_ptr() + lead, (nx, ny, nz), _lib.LNF_U16, r, xyz,
+                                        len(pts), out, None)
+            assert rc == _lib.LNF_OK
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want), (rule, lead)
+        _lib.lnf_destroy(h)
+
+
 # ---- Otsu's threshold and 2 sigma, found on the device ------------------------
 
 def _levels(dt, kind):
