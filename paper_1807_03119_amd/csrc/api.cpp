@@ -155,6 +155,7 @@ hipError_t launch_rule(int rule, uint32_t geom, const void* in, void* out, int d
                        Geom g, uint32_t gate, TileCfg cfg, hipStream_t s, TileCfg* plan,
                        const uint32_t* gate_dev)
 {
+    cfg.zs = std::min(cfg.zs, g.nz);  // a deeper strip is the whole volume; keeps the counts in int
     if (geom) return launch_geometry(rule, geom, in, out, dtype, r, g, gate, cfg.zs, s, plan, gate_dev);
     if (rule == LNF_MEAN9) return launch_mean9(in, out, dtype, r, g, gate, cfg, s, plan, gate_dev);
     return launch_minvar9(in, out, dtype, r, g, gate, cfg, s, plan, gate_dev);

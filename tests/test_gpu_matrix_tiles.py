@@ -248,6 +248,20 @@ def test_histogram_counts_do_not_carry_between_the_halves_of_a_word(value):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("rule", [_lib.LNF_MEAN9, _lib.LNF_MINVAR9])
+def test_strips_deeper_than_the_volume(rule):
+    """Any depth is accepted; one beyond the volume is one strip."""
+    from paper_1807_03119_amd.api import Filter
+    vol = _values((1024, 520, 2), np.uint8, "uniform", 77)
+    dev = torch.from_numpy(vol).cuda()
+    with Filter(rule, 0) as f:
+        want = f(dev, 1, zs=2).cpu().numpy()
+        for zs in (3, 2 ** 31 - 2, 2 ** 31 - 1):
+            for variant in (-1, 0, 1):
+                out = torch.zeros_like(dev)
+                assert np.array_equal(f(dev, 1, out=out, variant=variant, zs=zs).cpu().numpy(), want), (zs, variant)
+
+
 # ---- planes just below 4 GiB ---------------------------------------------------
 
 def _mean_at(vol, r, pts):
