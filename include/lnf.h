@@ -240,7 +240,12 @@ LNF_API int lnf_filter_batch_noalloc(lnf_handle h, const lnf_job* jobs, int n,
  */
 LNF_API int lnf_tune(lnf_handle h, const lnf_job* sample, int n);
 
-/* Write / read the context's tuned configurations (text, one per line). */
+/*
+ * Write / read the context's tuned configurations (text, one per line: key,
+ * variant, strip depth and the variant's tile width and height).  An entry
+ * whose tile shape is not that of its variant in this library, or that names
+ * none and could be of such a variant, is skipped on reading.
+ */
 LNF_API int lnf_tune_save(lnf_handle h, const char* path);
 LNF_API int lnf_tune_load(lnf_handle h, const char* path);
 

@@ -19,6 +19,15 @@ namespace {
 
 constexpr int kTimedRuns = 3;
 
+// The output tile that `variant` means for the rule and radius of a key.
+void key_tile_shape(TuneKey key, int variant, int* tx, int* ty)
+{
+    if ((int)(key >> 48) == LNF_MEAN9)
+        mean9_tile_shape(variant, tx, ty);
+    else
+        minvar9_tile_shape(variant, (int)(key >> 32 & 0xff), tx, ty);
+}
+
 std::vector<int> zs_candidates(int nz)
 {
     std::vector<int> c = {0};  // 0: the launcher's default depth
@@ -108,10 +117,13 @@ extern "C" int lnf_tune_save(lnf_handle h, const char* path)
     if (!f) return LNF_EINVAL;
     {
         std::lock_guard<std::mutex> lk(h->mu);
-        std::fprintf(f, "# lnf tune cache: key variant zs\n");
-        for (const auto& kv : h->tuned)
-            std::fprintf(f, "%llu %d %d\n", (unsigned long long)kv.first, kv.second.variant,
-                         kv.second.zs);
+        std::fprintf(f, "# lnf tune cache: key variant zs tile_width tile_height\n");
+        for (const auto& kv : h->tuned) {
+            int tx = 0, ty = 0;
+            key_tile_shape(kv.first, kv.second.variant, &tx, &ty);
+            std::fprintf(f, "%llu %d %d %d %d\n", (unsigned long long)kv.first, kv.second.variant,
+                         kv.second.zs, tx, ty);
+        }
     }
     return std::fclose(f) == 0 ? LNF_OK : LNF_EINVAL;
 }
@@ -127,8 +139,9 @@ extern "C" int lnf_tune_load(lnf_handle h, const char* path)
     while (std::fgets(line, sizeof line, f)) {
         if (line[0] == '#' || line[0] == '\n') continue;
         unsigned long long key = 0;
-        int v = 0, zs = 0;
-        if (std::sscanf(line, "%llu %d %d", &key, &v, &zs) != 3 || zs < 0 || v < -1) {
+        int v = 0, zs = 0, tx = 0, ty = 0;
+        const int fields = std::sscanf(line, "%llu %d %d %d %d", &key, &v, &zs, &tx, &ty);
+        if (fields < 3 || zs < 0 || v < -1) {
             rc = LNF_EINVAL;
             break;
         }
@@ -137,6 +150,16 @@ extern "C" int lnf_tune_load(lnf_handle h, const char* path)
         if (v >= nv) {
             rc = LNF_EINVAL;
             break;
+        }
+        // An entry is for the shape it was timed at.  Lines without one come from
+        // builds whose MEAN9 variants 1 and 3 were other tiles (64 x 32 and
+        // 32 x 32): those are not used, the default is.
+        if (fields >= 5 && v >= 0) {
+            int wx = 0, wy = 0;
+            key_tile_shape((TuneKey)key, v, &wx, &wy);
+            if (tx != wx || ty != wy) continue;
+        } else if (rule == LNF_MEAN9 && (v == 1 || v == 3)) {
+            continue;
         }
         got[(TuneKey)key] = TileCfg{v, zs};
     }

@@ -262,3 +262,31 @@ def test_batch_call_captured_in_a_graph_replays_exactly():
             graphs.append(g)
         assert codes == [_lib.LNF_OK, _lib.LNF_OK, _lib.LNF_EBUSY]
         del graphs
+
+
+def test_tune_entries_of_other_tile_shapes_are_skipped():
+    """A saved configuration is used for the tile shape it was timed at: not
+    where its variant has another shape, nor where an older file, without
+    shapes, names a variant that once had another."""
+    vol = torch.zeros((40, 40, 64), dtype=torch.uint8, device="cuda")
+    dims = (64, 40, 40)
+    with tempfile.TemporaryDirectory() as d:
+        path = os.path.join(d, "tune.txt")
+        with _filter("mean9") as f:
+            default = f.tile_config(dims, _lib.LNF_U8, 2)
+            f.tune([(vol, torch.empty_like(vol), 2)])
+            assert _lib.lnf_tune_save(f.handle, path) == 0
+            tuned = f.tile_config(dims, _lib.LNF_U8, 2)
+        key, variant, zs, tx, ty = [int(v) for ln in open(path) if not ln.startswith("#") for v in ln.split()]
+        shapes = {0: (64, 16), 1: (128, 32), 2: (32, 16), 3: (128, 16)}
+        assert (tx, ty) == shapes[variant] and tuned[0] == variant
+
+        def loaded(line):
+            open(path, "w").write(line + "\n")
+            with _filter("mean9") as g:
+                assert _lib.lnf_tune_load(g.handle, path) == 0
+                return g.tile_config(dims, _lib.LNF_U8, 2)
+        for v, (wx, wy) in shapes.items():
+            assert loaded(f"{key} {v} 7 {wx} {wy}") == (v, 7)
+            assert loaded(f"{key} {v} 7 {wx} {wy + 16}") == default
+            assert loaded(f"{key} {v} 7") == (default if v in (1, 3) else (v, 7))
