@@ -13,6 +13,7 @@
 // the matrix cores, in exact arithmetic, and slides a z-window through a
 // register ring while each wavefront streams down its z-strip (mean9_tile.h).
 #include <algorithm>
+#include <atomic>
 #include <vector>
 
 #include "device_common.h"
@@ -71,52 +72,97 @@ hipError_t dispatch_box(int r, const void* in, void* out, Geom g, uint32_t gate,
     }
 }
 
+constexpr int kMostResident = 10;  // most workgroups on a CU that times are kept for
+
 struct Variant {
-    int tx, ty, threads;
+    int tx, ty;
 };
 // output tiles of the compiled shapes
-constexpr Variant kVariants[] = {{64, 16, 256}, {128, 32, 512}, {32, 16, 128}, {128, 16, 512}};
+constexpr Variant kVariants[] = {{64, 16}, {128, 32}, {32, 16}, {128, 16}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
+template <int R, typename T>
+int resident_of_variant(int variant)
+{
+    const auto on_cu = [](const void* kernel, int threads) { return resident_groups(kernel, threads) / device_cus(); };
+    switch (variant) {
+    case 0: return on_cu((const void*)mean9_stream<R, 16, T, false, 64, false>, M9Geo<R, 16, 64, T>::THREADS);
+    case 1: return on_cu((const void*)mean9_stream<R, 32, T, false, 128, false>, M9Geo<R, 32, 128, T>::THREADS);
+    case 2: return on_cu((const void*)mean9_stream<R, 16, T, false, 32, false>, M9Geo<R, 16, 32, T>::THREADS);
+    default: return on_cu((const void*)mean9_stream<R, 16, T, false, 128, false>, M9Geo<R, 16, 128, T>::THREADS);
+    }
+}
+
+// Workgroups of a variant's kernel that a CU holds at once.
+int resident_of(int dtype, int r, int variant)
+{
+    static std::atomic<int> known[2][LNF_RADIUS_MAX][kNumVariants];  // 0: not asked yet
+    std::atomic<int>& k = known[dtype == LNF_U8][r - 1][variant];
+    int n = k.load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    const bool u8 = dtype == LNF_U8;
+    switch (r) {
+    case 1: n = u8 ? resident_of_variant<1, uint8_t>(variant) : resident_of_variant<1, uint16_t>(variant); break;
+    case 2: n = u8 ? resident_of_variant<2, uint8_t>(variant) : resident_of_variant<2, uint16_t>(variant); break;
+    case 3: n = u8 ? resident_of_variant<3, uint8_t>(variant) : resident_of_variant<3, uint16_t>(variant); break;
+    default: n = u8 ? resident_of_variant<4, uint8_t>(variant) : resident_of_variant<4, uint16_t>(variant); break;
+    }
+    n = std::max(1, std::min(n, kMostResident));
+    k.store(n, std::memory_order_relaxed);
+    return n;
+}
+
 // The default tile is the variant and strip depth with the least estimated
-// time: for each round of resident workgroups, iterations of a strip x time of
-// an iteration.  Iterations come in whole blocks of 2r+2 and include the 4r
-// slices of z-halo, the two of the pipeline.  at[n - 1] is the measured time of
-// an iteration (10.5 ns) with n workgroups on a CU, for n up to what the
-// registers let be resident; within 5 % the same for r = 1, 2, 3 and for the
-// shapes measured (128 x 256 x 200 to 256 x 256 x 150).  It steps where a SIMD
-// gets one wavefront more: the narrow tiles, whose workgroups are two
-// wavefronts, run four to a CU in little more than the time of one.
+// time: for each round of the workgroups that the CUs hold at once (resident_of:
+// uint16 64 x 16 tiles 4, 3, 3, 2 at r = 1..4, 32 x 16 twice that), iterations
+// of a strip, and 6 for its start, x time of an iteration.  Iterations come in
+// whole blocks of 2r+2 and include the 4r slices of z-halo, the two of the
+// pipeline.  at[n - 1] is the time of an iteration, in ns, with n workgroups on a
+// CU: medians over 450 random volumes (sides 48..800, 2^26 voxels at most, every
+// variant at up to 20 depths, the GPU kept busy), less 4 us for a launch.  It
+// steps where a SIMD gets one wavefront more: the narrow tiles, whose workgroups
+// are two wavefronts, run four to a CU in little more than the time of two.
 // Kept for rows that are staged and stored as whole words (mean9_words_ok) and
 // for others, which are shifted as they are read and stored.
+// On 250 other volumes the choice takes 1.3 % more than the best of the
+// times measured on average, 4 % more in nine of ten; on 70 of 2^26 to 2^28
+// voxels 1 %.
 struct TileCost {
-    int at[6];  // 0: not resident
+    int at[kMostResident];  // 0: never resident
 };
-constexpr TileCost kCostU16[2][kNumVariants] = {
-    {{{44, 61, 84, 111, 136}}, {{100}}, {{37, 51, 54, 59, 78, 85}}, {{67, 134}}},
-    {{{34, 48, 69, 92, 113}}, {{77}}, {{28, 41, 42, 47, 65, 70}}, {{46, 98}}}};
-constexpr TileCost kCostU8[2][kNumVariants] = {
-    {{{29, 38, 52, 65, 82}}, {{61}}, {{26, 33, 34, 36, 50, 61}}, {{44, 76}}},
-    {{{22, 28, 40, 51, 66}}, {{40}}, {{19, 24, 26, 28, 38, 48}}, {{30, 53}}}};
-// At r = 4 the rings take more registers, so fewer workgroups are resident.
-constexpr int kResidentU16R4[kNumVariants] = {2, 1, 4, 1}, kResidentU8R4[kNumVariants] = {3, 1, 6, 1};
+// [r - 1][whole words][variant]
+constexpr TileCost kCostU16[LNF_RADIUS_MAX][2][kNumVariants] = {
+    {{{{393, 512, 670, 842}}, {{854}}, {{358, 467, 470, 506, 658, 800, 807, 842}}, {{579, 960}}},
+     {{{299, 395, 534, 673}}, {{673}}, {{279, 379, 379, 406, 537, 664, 677, 704}}, {{397, 662}}}},
+    {{{{398, 527, 705}}, {{849}}, {{350, 450, 468, 489, 660, 688}}, {{545}}},
+     {{{326, 423, 582}}, {{671}}, {{280, 379, 385, 408, 557, 575}}, {{397}}}},
+    {{{{402, 545, 735}}, {{876}}, {{349, 461, 474, 521, 685, 708}}, {{594}}},
+     {{{328, 433, 598}}, {{685}}, {{281, 381, 381, 413, 567, 605}}, {{438}}}},
+    {{{{447, 605}}, {{1684}}, {{370, 516, 530, 576}}, {{666}}},
+     {{{352, 494}}, {{1179}}, {{310, 452, 454, 496}}, {{489}}}}};
+constexpr TileCost kCostU8[LNF_RADIUS_MAX][2][kNumVariants] = {
+    {{{{279, 340, 431, 537, 641}}, {{515, 839}}, {{251, 298, 307, 314, 416, 501, 509, 530, 615, 645}}, {{383, 622}}},
+     {{{225, 261, 348, 434, 521}}, {{351, 591}}, {{187, 232, 235, 243, 334, 404, 411, 432, 507, 537}}, {{271, 424}}}},
+    {{{{276, 338, 433, 535}}, {{509}}, {{250, 303, 309, 318, 413, 511, 512, 534}}, {{390, 622}}},
+     {{{220, 256, 343, 435}}, {{370}}, {{188, 230, 233, 249, 330, 401, 405, 428}}, {{276, 434}}}},
+    {{{{280, 331, 443, 549}}, {{530}}, {{257, 310, 317, 337, 436, 526, 541, 570}}, {{411, 657}}},
+     {{{219, 256, 343, 439}}, {{364}}, {{197, 240, 258, 309, 399, 435, 493, 547}}, {{268, 434}}}},
+    {{{{297, 377, 502}}, {{643}}, {{271, 340, 352, 370, 491, 511}}, {{434}}},
+     {{{247, 297, 403}}, {{429}}, {{221, 270, 276, 307, 414, 432}}, {{288}}}}};
 
 // whether rows start at whole words, given volumes that do
 int row_words(int dtype, int nx) { return nx % (dtype == LNF_U8 ? 4 : 2) == 0; }
 
-TileCost cost_of(int dtype, int variant, int r, Geom g)
+const TileCost& cost_of(int dtype, int variant, int r, Geom g)
 {
-    const int words = row_words(dtype, g.nx);
-    TileCost c = dtype == LNF_U8 ? kCostU8[words][variant] : kCostU16[words][variant];
-    if (r == 4)
-        for (int n = dtype == LNF_U8 ? kResidentU8R4[variant] : kResidentU16R4[variant]; n < 6; ++n) c.at[n] = 0;
-    return c;
+    return (dtype == LNF_U8 ? kCostU8 : kCostU16)[r - 1][row_words(dtype, g.nx)][variant];
 }
 
-int resident_of(const TileCost& c)
+// The resident workgroups that the table has times for.
+int priced_residents(const TileCost& c, int dtype, int r, int variant)
 {
-    int n = 1;
-    while (n < 6 && c.at[n]) ++n;
+    int n = resident_of(dtype, r, variant);
+    while (n > 1 && !c.at[n - 1]) --n;
     return n;
 }
 
@@ -150,6 +196,8 @@ int tile_iterations(int zs, int r)
 }
 
 // Whether `variant` is one to consider when `want` is asked for.
+// 128 x 32 at r = 4 on uint16 only then: 18 ring values of 8 outputs do not fit
+// the registers (120 spills; an output takes 1.2 to 1.5 times that of 128 x 16).
 bool tile_eligible(int variant, int want, int dtype, int r)
 {
     if (want >= 0 && want < kNumVariants) return variant == want;
@@ -164,8 +212,9 @@ TileCfg resolve_tile(TileCfg want, int dtype, int r, Geom g)
     const int cus = device_cus(), most = std::max(1, g.nz / 4);  // strips of 4 slices at least
     for (int v = 0; v < kNumVariants; ++v) {
         if (!tile_eligible(v, want.variant, dtype, r)) continue;
-        const TileCost c = cost_of(dtype, v, r, g);
-        const int resident = resident_of(c), percent = traffic_percent(dtype, v, (double)g.nx * g.ny * g.nz);
+        const TileCost& c = cost_of(dtype, v, r, g);
+        const int resident = priced_residents(c, dtype, r, v);
+        const int percent = traffic_percent(dtype, v, (double)g.nx * g.ny * g.nz);
         const int cols = (int)std::min<long long>(tile_groups(v, g.nz, g), 1 << 24);
         // strip counts that fill whole rounds: one round of 1 .. resident
         // workgroups per CU, or up to four full ones
@@ -177,14 +226,13 @@ TileCfg resolve_tile(TileCfg want, int dtype, int r, Geom g)
             nzs = (g.nz + zs - 1) / zs;
             const int groups = (int)std::min<long long>((long long)cols * nzs, 1 << 30);
             const int n = (groups + cus - 1) / cus;  // workgroups of a CU
-            const int time = n / resident * c.at[resident - 1] + (n % resident ? c.at[n % resident - 1] : 0);
-            // a further round starts with its weights and first slices: 3 iterations
-            const double cost =
-                ((double)time * tile_iterations(zs, r) + (n - 1) / resident * 3 * c.at[resident - 1]) * percent;
+            const double time = (double)(n / resident) * c.at[resident - 1] + (n % resident ? c.at[n % resident - 1] : 0);
+            const double cost = time * (tile_iterations(zs, r) + 6) * percent;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = TileCfg{v, zs};
             }
+            if (want.zs > 0 || nzs >= most) break;  // no other depth follows
         }
     }
     return best;
@@ -278,7 +326,7 @@ TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>&
         for (const Geom& q : g) {
             const int words = row_words(dtype, q.nx);
             const BatchCost c = dtype == LNF_U8 ? kBatchU8[words][v] : kBatchU16[words][v];
-            const int resident = r == 4 ? (dtype == LNF_U8 ? kResidentU8R4 : kResidentU16R4)[v] : c.resident;
+            const int resident = std::min(c.resident, resident_of(dtype, r, v));
             const float tau = (float)(c.one + (resident - 1) * c.more);
             const float cols = (float)tile_groups(v, q.nz, q) * tau / resident;
             for (int i = 0; i < 8; ++i) {
