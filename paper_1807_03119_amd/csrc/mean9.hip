@@ -14,6 +14,7 @@
 // register ring while each wavefront streams down its z-strip (mean9_tile.h).
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <vector>
 
 #include "device_common.h"
@@ -300,19 +301,19 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
 
 int mean9_variants() { return kNumVariants; }
 
-// The tile and strip depth of a batch class: work spread over the CUs and a
-// tail of the longest strip.  Each volume pushes the others out of the caches,
-// which costs the narrow tiles more than alone (64 volumes of 64^3 to 384^3:
-// 857 us with these times of an iteration, 1049 us with those of single calls,
-// which prefer 32 x 16): {with one workgroup on a CU, more for each further
-// one, resident}.
-struct BatchCost {
-    int one, more, resident;
-};
-constexpr BatchCost kBatchU16[2][kNumVariants] = {{{38, 22, 3}, {104, 0, 1}, {36, 12, 6}, {64, 0, 1}},
-                                                  {{36, 20, 3}, {84, 0, 1}, {33, 12, 6}, {50, 0, 1}}};
-constexpr BatchCost kBatchU8[2][kNumVariants] = {{{30, 10, 4}, {62, 0, 1}, {28, 8, 8}, {44, 20, 2}},
-                                                 {{28, 9, 4}, {48, 0, 1}, {26, 8, 8}, {36, 20, 2}}};
+// The tile and strip depth of a batch class, by estimated time.  Strips: with no
+// more workgroups than the CUs hold, the longest strip at the time of an
+// iteration with that many; else all strips spread over the CUs, and a tail of
+// three quarters of the longest strip alone (3 iterations for the start of
+// each).  Memory: kTraffic input sizes at 4.6 GB/ms for what a tile shape fetches
+// beside its outputs, half of it below 2^27 voxels.  The estimate is the root of
+// the two squares, since neither hides the other.  In a batch the 128-wide tiles
+// take 8 % longer than the tables above, the 32-wide 5 %.
+// From 240 random batches of one class (2 to 24 volumes with sides of 32 to
+// 520), every variant at eight depths: of those above 60 us the choice
+// takes 4.5 % more than the best of the times on average (with times fitted to
+// one batch of 64 volumes, 10 %).
+constexpr float kTraffic[kNumVariants] = {2.4f, 1.6f, 4.f, 1.6f}, kInBatch[kNumVariants] = {1.f, 1.08f, 1.05f, 1.08f};
 
 TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>& g)
 {
@@ -320,27 +321,33 @@ TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>&
     TileCfg best{0, 16};
     float best_cost = -1.f;
     const float cus = (float)device_cus();
+    double voxels = 0;
+    for (const Geom& q : g) voxels += (double)q.nx * q.ny * q.nz;
+    const double passes = voxels * (dtype == LNF_U8 ? 1 : 2) / 4600.0 * (voxels < 134217728.0 ? 0.5 : 1.0);
     for (int v = 0; v < kNumVariants; ++v) {
         if (!tile_eligible(v, variant, dtype, r)) continue;
-        float work[8] = {}, longest[8] = {};
-        for (const Geom& q : g) {
-            const int words = row_words(dtype, q.nx);
-            const BatchCost c = dtype == LNF_U8 ? kBatchU8[words][v] : kBatchU16[words][v];
-            const int resident = std::min(c.resident, resident_of(dtype, r, v));
-            const float tau = (float)(c.one + (resident - 1) * c.more);
-            const float cols = (float)tile_groups(v, q.nz, q) * tau / resident;
-            for (int i = 0; i < 8; ++i) {
-                const int nzs = (q.nz + kDepths[i] - 1) / kDepths[i];
-                const float iters = (float)tile_iterations((q.nz + nzs - 1) / nzs, r);
-                work[i] += cols * nzs * iters;
-                longest[i] = std::max(longest[i], tau * iters);
+        const float memory = (float)passes * kTraffic[v];
+        for (int depth : kDepths) {
+            float groups = 0.f;
+            for (const Geom& q : g) groups += (float)tile_groups(v, depth, q);
+            float work = 0.f, longest = 0.f, alone = 0.f;
+            bool rounds = false;
+            for (const Geom& q : g) {
+                const TileCost& c = cost_of(dtype, v, r, q);
+                const int resident = priced_residents(c, dtype, r, v);
+                const int n = (int)std::min((groups + cus - 1.f) / cus, (float)resident);
+                const int nzs = (q.nz + depth - 1) / depth;
+                const float iters = (float)(tile_iterations((q.nz + nzs - 1) / nzs, r) + 3);
+                rounds = groups > cus * resident;
+                work += (float)tile_groups(v, depth, q) * iters * c.at[resident - 1] / resident;
+                longest = std::max(longest, iters * c.at[n - 1]);
+                alone = std::max(alone, iters * c.at[0]);
             }
-        }
-        for (int i = 0; i < 8; ++i) {
-            const float cost = work[i] / cus + longest[i];
+            float cost = rounds ? std::max(work / cus + 0.75f * alone, longest) : longest;
+            cost = std::hypot(cost * kInBatch[v], memory);
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
-                best = TileCfg{v, kDepths[i]};
+                best = TileCfg{v, depth};
             }
         }
     }
