@@ -13,7 +13,6 @@
 // the matrix cores, in exact arithmetic, and slides a z-window through a
 // register ring while each wavefront streams down its z-strip (mean9_tile.h).
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <vector>
 
@@ -73,7 +72,7 @@ hipError_t dispatch_box(int r, const void* in, void* out, Geom g, uint32_t gate,
     }
 }
 
-constexpr int kMostResident = 10;  // most workgroups on a CU that times are kept for
+constexpr int kMostResident = 10;  // most workgroups of a tile kernel on a CU
 
 struct Variant {
     int tx, ty;
@@ -82,41 +81,10 @@ struct Variant {
 constexpr Variant kVariants[] = {{64, 16}, {128, 32}, {32, 16}, {128, 16}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-template <int R, typename T>
-int resident_of_variant(int variant)
-{
-    const auto on_cu = [](const void* kernel, int threads) { return resident_groups(kernel, threads) / device_cus(); };
-    switch (variant) {
-    case 0: return on_cu((const void*)mean9_stream<R, 16, T, false, 64, false>, M9Geo<R, 16, 64, T>::THREADS);
-    case 1: return on_cu((const void*)mean9_stream<R, 32, T, false, 128, false>, M9Geo<R, 32, 128, T>::THREADS);
-    case 2: return on_cu((const void*)mean9_stream<R, 16, T, false, 32, false>, M9Geo<R, 16, 32, T>::THREADS);
-    default: return on_cu((const void*)mean9_stream<R, 16, T, false, 128, false>, M9Geo<R, 16, 128, T>::THREADS);
-    }
-}
-
-// Workgroups of a variant's kernel that a CU holds at once.
-int resident_of(int dtype, int r, int variant)
-{
-    static std::atomic<int> known[2][LNF_RADIUS_MAX][kNumVariants];  // 0: not asked yet
-    std::atomic<int>& k = known[dtype == LNF_U8][r - 1][variant];
-    int n = k.load(std::memory_order_relaxed);
-    if (n > 0) return n;
-    const bool u8 = dtype == LNF_U8;
-    switch (r) {
-    case 1: n = u8 ? resident_of_variant<1, uint8_t>(variant) : resident_of_variant<1, uint16_t>(variant); break;
-    case 2: n = u8 ? resident_of_variant<2, uint8_t>(variant) : resident_of_variant<2, uint16_t>(variant); break;
-    case 3: n = u8 ? resident_of_variant<3, uint8_t>(variant) : resident_of_variant<3, uint16_t>(variant); break;
-    default: n = u8 ? resident_of_variant<4, uint8_t>(variant) : resident_of_variant<4, uint16_t>(variant); break;
-    }
-    n = std::max(1, std::min(n, kMostResident));
-    k.store(n, std::memory_order_relaxed);
-    return n;
-}
-
 // The default tile is the variant and strip depth with the least estimated
-// time: for each round of the workgroups that the CUs hold at once (resident_of:
-// uint16 64 x 16 tiles 4, 3, 3, 2 at r = 1..4, 32 x 16 twice that), iterations
-// of a strip, and 6 for its start, x time of an iteration.  Iterations come in
+// time: for each round of the workgroups that the CUs hold at once (as many as a
+// row of the table has entries: the kernels' occupancy), iterations of a strip,
+// and 6 for its start, x time of an iteration.  Iterations come in
 // whole blocks of 2r+2 and include the 4r slices of z-halo, the two of the
 // pipeline.  at[n - 1] is the time of an iteration, in ns, with n workgroups on a
 // CU: medians over 450 random volumes (sides 48..800, 2^26 voxels at most, every
@@ -159,11 +127,11 @@ const TileCost& cost_of(int dtype, int variant, int r, Geom g)
     return (dtype == LNF_U8 ? kCostU8 : kCostU16)[r - 1][row_words(dtype, g.nx)][variant];
 }
 
-// The resident workgroups that the table has times for.
-int priced_residents(const TileCost& c, int dtype, int r, int variant)
+// Workgroups of the variant's kernel that a CU holds at once.
+int resident_of(const TileCost& c)
 {
-    int n = resident_of(dtype, r, variant);
-    while (n > 1 && !c.at[n - 1]) --n;
+    int n = 1;
+    while (n < kMostResident && c.at[n]) ++n;
     return n;
 }
 
@@ -214,7 +182,7 @@ TileCfg resolve_tile(TileCfg want, int dtype, int r, Geom g)
     for (int v = 0; v < kNumVariants; ++v) {
         if (!tile_eligible(v, want.variant, dtype, r)) continue;
         const TileCost& c = cost_of(dtype, v, r, g);
-        const int resident = priced_residents(c, dtype, r, v);
+        const int resident = resident_of(c);
         const int percent = traffic_percent(dtype, v, (double)g.nx * g.ny * g.nz);
         const int cols = (int)std::min<long long>(tile_groups(v, g.nz, g), 1 << 24);
         // strip counts that fill whole rounds: one round of 1 .. resident
@@ -334,7 +302,7 @@ TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>&
             bool rounds = false;
             for (const Geom& q : g) {
                 const TileCost& c = cost_of(dtype, v, r, q);
-                const int resident = priced_residents(c, dtype, r, v);
+                const int resident = resident_of(c);
                 const int n = (int)std::min((groups + cus - 1.f) / cus, (float)resident);
                 const int nzs = (q.nz + depth - 1) / depth;
                 const float iters = (float)(tile_iterations((q.nz + nzs - 1) / nzs, r) + 3);
