@@ -3,11 +3,12 @@
 // inside the renderer (Section "Our Method"; Results, Performance), so the
 // work is a sparse gather rather than a dense stencil.
 //
-// Sixteen lanes per point, four neighbouring points of the list per wavefront
-// (lane % 4, so that points beside each other, which share most of their rows,
-// read the same cache lines in one instruction).  The nine clusters cover the
+// Sixteen lanes per point (sixty-four in a short list, see launch_points_r), four
+// neighbouring points of the list per wavefront (lane % 4, so that points beside
+// each other, which share most of their rows, read the same cache lines in one
+// instruction).  The nine clusters cover the
 // (4r+1)^3 block around the point (coordinates clamped into the volume); the
-// sixteen lanes split its (4r+1)^2 x-rows.  A row is read as the r * sizeof(T)
+// lanes split its (4r+1)^2 x-rows.  A row is read as the r * sizeof(T)
 // + 1 aligned words that hold its 4r+1 voxels, for every alignment of a voxel,
 // and shifted into place; rows that leave the volume in x, and uint16 volumes
 // at an odd address, are read voxel by voxel.
@@ -22,7 +23,8 @@
 // What bounds it: the rows' cache-line requests (169 rows a point at r = 3).
 // One wavefront per point with 13 two-byte loads a row took 925 us for the
 // 262144 rays of a 512^3 uint16 volume (r = 3, MEAN9); this takes 179 (MINVAR9
-// 969 and 222).  Scattered points are bound by their cache misses (995 -> 905).
+// 969 and 222).  Scattered points are bound by their cache misses (2^20 of 512 x
+// 512 x 256 uint16, r = 1..4: 454 -> 473, 1516 -> 1558, 3960 -> 3470, 12480 -> 6160).
 //
 // The first-hit pass produces that point list for rays parallel to z: per
 // pixel (x, y), the first voxel of the column, in the ray's direction, whose
@@ -45,16 +47,14 @@
 namespace lnf {
 namespace {
 
-constexpr int kPointLanes = 16;                 // lanes per point
 constexpr int kPointThreads = 256;
-constexpr int kGroupPoints = kPointThreads / kPointLanes;
 
-// Sum over the sixteen lanes of a point (lane bits 2 to 5).
-template <typename V>
+// Sum over the LANES lanes of a point (the upper lane bits).
+template <int LANES, typename V>
 __device__ __forceinline__ V point_sum(V v)
 {
 #pragma unroll
-    for (int off = 4; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+    for (int off = 64 / LANES; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
     return v;
 }
 
@@ -74,7 +74,7 @@ constexpr uint32_t row_weights(int a)
     return w;
 }
 
-template <int R, typename T, int RULE>
+template <int R, typename T, int RULE, int LANES>
 __global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
     const T* __restrict__ in, Geom g, const int32_t* __restrict__ xyz, int64_t n, uint32_t gate,
     uint32_t* __restrict__ out)
@@ -86,9 +86,10 @@ __global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
     constexpr bool VAR = RULE == LNF_MINVAR9;
     // squares: uint32 holds a cluster's for uint8 (729 * 255^2), fp64 for uint16
     using Q = std::conditional_t<sizeof(T) == 1, uint32_t, double>;
-    const int lane = threadIdx.x & 63, sub = lane >> 2;
-    const int64_t pi = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kGroupPoints +
-                       (threadIdx.x >> 6) * 4 + (lane & 3);
+    constexpr int kWave = 64 / LANES;  // points of a wavefront
+    const int lane = threadIdx.x & 63, sub = lane / kWave;
+    const int64_t pi = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * (kPointThreads / LANES) +
+                       (threadIdx.x >> 6) * kWave + lane % kWave;
     const int64_t p = pi < n ? pi : n - 1;  // lanes past the list redo its last point
     int px = xyz[3 * p], py = xyz[3 * p + 1], pz = xyz[3 * p + 2];
     const bool inside = px >= 0 && py >= 0 && pz >= 0 && px < g.nx && py < g.ny && pz < g.nz;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
     }
     int dy = sub % W - 2 * R, dz = sub / W - 2 * R;
     // points outside the volume read nothing
-    for (int row = inside ? sub : NROW; row < NROW; row += kPointLanes) {
+    for (int row = inside ? sub : NROW; row < NROW; row += LANES) {
         const int y = clampi(py + dy, 0, g.ny - 1), z = clampi(pz + dz, 0, g.nz - 1);
         const T* rp = in + (size_t)z * plane + (size_t)y * nx;
         uint32_t w[ND];  // packed voxels from px - 2R on
@@ -173,9 +174,9 @@ __global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
                 q[j + 1] += in_yz ? qside[j & 1] : (Q)0;
             }
         }
-        // the row kPointLanes further on
-        dy += kPointLanes % W;
-        dz += kPointLanes / W;
+        // the row LANES further on
+        dy += LANES % W;
+        dz += LANES / W;
         if (dy > 2 * R) {
             dy -= W;
             dz += 1;
@@ -183,12 +184,12 @@ __global__ __launch_bounds__(kPointThreads) void filter_points_kernel(
     }
     uint32_t o;
     if constexpr (!VAR) {
-        o = round_div_odd(point_sum(s[0]), 1.0 / (9.0 * NB));
+        o = round_div_odd(point_sum<LANES>(s[0]), 1.0 / (9.0 * NB));
     } else {
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            s[k] = point_sum(s[k]);
-            q[k] = point_sum(q[k]);
+            s[k] = point_sum<LANES>(s[k]);
+            q[k] = point_sum<LANES>(q[k]);
         }
         uint32_t best_s = s[0];
         double best_v = __builtin_fma((double)NB, (double)q[0], -(double)s[0] * (double)s[0]);
@@ -260,19 +261,32 @@ hipError_t launch_first_hit(const void* vol, Geom g, uint32_t thr, int direction
     return hipGetLastError();
 }
 
+template <int R, typename T, int LANES>
+hipError_t launch_points_lanes(int rule, const void* vol, Geom g, const int32_t* xyz, int64_t n,
+                               uint32_t gate, uint32_t* out, hipStream_t s)
+{
+    constexpr int kGroup = kPointThreads / LANES;
+    const dim3 grid((unsigned)((n + kGroup - 1) / kGroup)), block(kPointThreads);
+    const T* in = static_cast<const T*>(vol);
+    if (rule == LNF_MEAN9)
+        hipLaunchKernelGGL((filter_points_kernel<R, T, LNF_MEAN9, LANES>), grid, block, 0, s, in, g,
+                           xyz, n, gate, out);
+    else
+        hipLaunchKernelGGL((filter_points_kernel<R, T, LNF_MINVAR9, LANES>), grid, block, 0, s, in, g,
+                           xyz, n, gate, out);
+    return hipGetLastError();
+}
+
+// Sixteen lanes a point, but a wavefront for lists of up to two points a SIMD from
+// r = 2: they leave the chip idle, and a point's rows are one chain for its lanes
+// (1024 scattered points of uint16, sixteen lanes against sixty-four: r = 2 4.9 and
+// 3.3 us, r = 4 21.2 and 9.3; 4096 rays' hits side by side, r = 4: 22.1 and 35.5).
 template <int R, typename T>
 hipError_t launch_points_r(int rule, const void* vol, Geom g, const int32_t* xyz, int64_t n,
                            uint32_t gate, uint32_t* out, hipStream_t s)
 {
-    const dim3 grid((unsigned)((n + kGroupPoints - 1) / kGroupPoints)), block(kPointThreads);
-    const T* in = static_cast<const T*>(vol);
-    if (rule == LNF_MEAN9)
-        hipLaunchKernelGGL((filter_points_kernel<R, T, LNF_MEAN9>), grid, block, 0, s, in, g, xyz,
-                           n, gate, out);
-    else
-        hipLaunchKernelGGL((filter_points_kernel<R, T, LNF_MINVAR9>), grid, block, 0, s, in, g,
-                           xyz, n, gate, out);
-    return hipGetLastError();
+    if (R >= 2 && n <= 8 * device_cus()) return launch_points_lanes<R, T, 64>(rule, vol, g, xyz, n, gate, out, s);
+    return launch_points_lanes<R, T, 16>(rule, vol, g, xyz, n, gate, out, s);
 }
 
 template <typename T>

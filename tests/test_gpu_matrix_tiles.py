@@ -136,6 +136,32 @@ def test_points_at_faces_and_alignments(dt, r):
 
 
 @pytest.mark.parametrize("r", [1, 2, 3, 4])
+@pytest.mark.parametrize("dt", ["u8", "u16"])
+def test_points_lists_of_every_lane_split(dt, r):
+    """Lists around two points a SIMD, where a point's rows go from sixty-four
+    lanes to sixteen, and one that does not fill its last wavefront."""
+    from paper_1807_03119_amd.api import Filter
+    tdt, ndt = DTYPES[dt]
+    vol = _values((37, 21, 13), ndt, "uniform", 7300 + r)
+    nz, ny, nx = vol.shape
+    edge = 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(r)
+    pts = np.stack([rng.integers(0, m, edge + 70) for m in (nx, ny, nz)], 1)
+    pts[::97] = [nx, 0, 0]
+    inside = pts[:, 0] < nx
+    for rule, orule in ((_lib.LNF_MEAN9, oracle.MEAN9), (_lib.LNF_MINVAR9, oracle.MINVAR9)):
+        want = np.full(len(pts), 0xFFFFFFFF, np.uint32)
+        want[inside] = oracle.filter_points(vol, r, pts[inside], orule)
+        with Filter(rule, 0) as f:
+            for lead in range(4 // ndt().itemsize):
+                dev = _at_offset(vol, tdt, lead)
+                for n in (3, edge - 1, edge, edge + 1, edge + 70):
+                    xyz = torch.from_numpy(pts[:n].astype(np.int32)).cuda()
+                    got = f.points(dev, r, xyz).cpu().numpy().view(np.uint32)
+                    assert np.array_equal(got, want[:n]), (rule, lead, n)
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
 def test_points_of_a_uint16_volume_at_an_odd_address(r):
     """The C interface takes any byte address; a row's last voxel may then end
     past the words that hold a row of an even address."""
