@@ -338,7 +338,7 @@ int batch_launch(lnf_ctx* h, const lnf_job* jobs, int n, const std::vector<Geom>
             } else {
                 variant = cfg.variant >= 0 && cfg.variant < minvar9_variants()
                               ? cfg.variant
-                              : minvar9_default_variant(dtype, r, geoms[order[k]]);
+                              : minvar9_batch_variant(r, geoms[order[k]]);
                 minvar9_tile_shape(variant, r, &tx, &ty);
             }
             kern[c] = class_kernel(h->rule, c, h->gate != 0, variant, queue);

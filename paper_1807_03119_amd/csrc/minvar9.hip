@@ -61,12 +61,44 @@ hipError_t launch_variant(int variant, const void* in, void* out, Geom g, uint32
     return launch_planes<R, T, false>(in, out, g, gate, zs, s, plan, gate_dev);
 }
 
+// Estimated time of a launch, in rounds of the workgroups that the CUs hold at
+// once x slices: a round that is not full still takes 0.4 of a full one, and a
+// strip 8 slices more than its depth.  `round`: a full round of this tile, of
+// the narrow tile's.
+template <int R, typename T, bool WT>
+double planes_cost(Geom g, double round)
+{
+    using S = MV9Shape<R, WT>;
+    const int tiles = ((g.nx + S::TX - 1) / S::TX) * ((g.ny + S::TY - 1) / S::TY);
+    const int resident = resident_groups((const void*)minvar9_planes<R, T, false, WT>, S::THREADS);
+    const int zs = default_zs(tiles, g.nz, resident), cus = device_cus(), per_cu = resident / cus;
+    const long long groups = (long long)tiles * ((g.nz + zs - 1) / zs);
+    const long long n = (groups + cus - 1) / cus, rest = n % per_cu;
+    return ((double)(n / per_cu) + (rest ? 0.4 + 0.6 * (double)rest / per_cu : 0.0)) * (zs + 8) * round;
+}
+
+// The tile with the least estimated time.  A full round of wide tiles (2 to 4 on a
+// CU) takes 0.92 to 1.06 of one of narrow tiles (4 to 7), for the same outputs
+// from r = 2, so what decides is how well either fills its rounds and the rows: of
+// 500 random volumes (sides 48..900) the choice is on average within 0.2 % of the
+// faster tile; wide from 256 x 256 on was 2 to 4 % off (uint8 r = 2, 391 x 585 x
+// 251: 171 and 210 us, 716 x 370 x 31 41 and 49; r = 3, 512^3: 362 and 353).
+template <typename T>
+int faster_variant(int r, Geom g)
+{
+    switch (r) {
+    case 1: return planes_cost<1, T, true>(g, 1.06) < planes_cost<1, T, false>(g, 1.0);
+    case 2: return planes_cost<2, T, true>(g, 0.96) < planes_cost<2, T, false>(g, 1.0);
+    case 3: return planes_cost<3, T, true>(g, 0.92) < planes_cost<3, T, false>(g, 1.0);
+    default: return 0;  // one shape
+    }
+}
+
 template <typename T>
 hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, TileCfg cfg,
                       hipStream_t s, TileCfg* plan, const uint32_t* gate_dev)
 {
-    const int v = cfg.variant >= 0 ? cfg.variant
-                                   : minvar9_default_variant(sizeof(T) == 1 ? LNF_U8 : LNF_U16, r, g);
+    const int v = cfg.variant >= 0 ? cfg.variant : faster_variant<T>(r, g);
     if (plan) plan->variant = v;
     switch (r) {
     case 1: return launch_variant<1, T>(v, in, out, g, gate, cfg.zs, s, plan, gate_dev);
@@ -83,13 +115,11 @@ hipError_t dispatch_r(const void* in, void* out, int r, Geom g, uint32_t gate, T
 // r = 3; the same tile as 0 at r = 4)
 int minvar9_variants() { return 2; }
 
-// The wide tile on large planes up to r = 3 (uint8: r = 1 274 -> 257 us, r = 2
-// 365 -> 352 on 512^3), else 32 x 16.
-int minvar9_default_variant(int dtype, int r, Geom g)
-{
-    (void)dtype;
-    return (g.nx >= 256 && g.ny >= 256 && r <= 3) ? 1 : 0;
-}
+// In the launch of a batch the narrow tile is the faster up to r = 2 (60 random
+// classes of 1 to 24 volumes: the wide one 3 to 28 % slower, 10 % on average);
+// at r = 3 they are within a few percent, the wide one ahead where volumes are
+// large (24 of 256 to 400, uint16: 3350 and 3184 us).
+int minvar9_batch_variant(int r, Geom g) { return r == 3 && g.nx >= 256 && g.ny >= 256 ? 1 : 0; }
 
 void minvar9_tile_shape(int variant, int r, int* tx, int* ty)
 {

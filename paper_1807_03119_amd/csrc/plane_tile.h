@@ -88,8 +88,7 @@ constexpr int pt_pitch(int ys, int g, int lo, int m, bool two_mod4)
 
 // WT (wide tile): MINVAR9 cubes at offset r up to r = 3 fit 4 waves per SIMD,
 // so 64 x 16 tiles in 512-thread workgroups cost less halo at the same
-// occupancy: faster on large uint16 planes (r = 3: 214 -> 228 Gvox/s), slower
-// on small volumes and on uint8 at r = 2.  A tile variant, chosen per launch.
+// occupancy.  A tile variant, chosen per launch by estimated time (minvar9.hip).
 template <int R, int D, int SHAPE, int RULE, bool WT = false>
 struct PTShape {
     static constexpr bool CROSS = SHAPE == kClusterCross;
