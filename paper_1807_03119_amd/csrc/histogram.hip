@@ -56,13 +56,15 @@ __global__ __launch_bounds__(kThreads) void hist_u8(const uint8_t* __restrict__ 
 
 // Chunk c of a workgroup is vectors [(c * gridDim + block) * cv, ... + cv) past
 // the first 16-byte boundary, cv <= kVecs16; block 0's first chunk also takes
-// the voxels before that boundary and after the last vector.  512^3 12-bit:
-// 117 -> 71 us against a flush per chunk, 1024x1024x512 398 -> 227.
+// the voxels before that boundary and after the last vector.  One flush for all
+// chunks, a bin a lane (512 adjacent bytes an atomic instruction; both bins of a
+// word by one lane meet 1 KiB): 512^3 of 12 bits 117 us with a flush per chunk,
+// 71 with one, 59 with adjacent lanes; 2^25 voxels of 16 bits 570, 324 and 123.
 __global__ __launch_bounds__(kThreads16) void hist_u16(const uint16_t* __restrict__ in, size_t n,
                                                         unsigned long long* hist, int cv, int chunks)
 {
     constexpr int kLoads = 4, kWords = 32768 / kThreads16;
-    __shared__ uint32_t pairs[32768];  // bin 2i in the low half, bin 2i+1 in the high half
+    __shared__ __align__(16) uint32_t pairs[32768];  // bin 2i in the low half, bin 2i+1 in the high half
     const int tid = threadIdx.x;
 #pragma unroll
     for (int k = 0; k < kWords; ++k) pairs[tid + k * kThreads16] = 0;
@@ -110,6 +112,25 @@ __global__ __launch_bounds__(kThreads16) void hist_u16(const uint16_t* __restric
                 }
             }
         barrier_lds();
+        if (chunks == 1) {
+            // the only chunk: straight from LDS, a bin a lane, so that an atomic
+            // instruction meets 512 adjacent bytes; 512 empty bins are passed over
+            // at once, and each workgroup starts at another part of the bins
+            const int lane = tid & 63;
+#pragma unroll 2
+            for (int k = 0; k < kWords / 4; ++k) {
+                const int q = tid - lane + (int)((k + blockIdx.x) % (kWords / 4)) * kThreads16;
+                const uint4 w4 = reinterpret_cast<const uint4*>(pairs)[q + lane];
+                if (!__any((w4.x | w4.y | w4.z | w4.w) != 0)) continue;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int i = 8 * q + 64 * j + lane;
+                    const uint32_t w = pairs[i >> 1], count = (i & 1) ? w >> 16 : w & 0xffffu;
+                    if (count) atomicAdd(&hist[i], (unsigned long long)count);
+                }
+            }
+            return;
+        }
         int t = tid;  // opaque: the addresses are formed here, not kept over the loop
         asm volatile("" : "+v"(t));
 #pragma unroll
@@ -122,18 +143,18 @@ __global__ __launch_bounds__(kThreads16) void hist_u16(const uint16_t* __restric
         }
         barrier_lds();
     }
-    int t = tid;
-    asm volatile("" : "+v"(t));
+    // as above, a bin a lane: the wavefront's words hold two bins each, which go
+    // to neighbouring lanes (selection by mask: the counts stay 32-bit registers)
+    const int lane = tid & 63, base = 2 * (tid - lane) + lane;
+    const bool odd = lane & 1;
 #pragma unroll
-    for (int k = 0; k < kWords; ++k) {
-        // copied where the compiler does not see it, or it keeps every count in
-        // the register pair that the 64-bit atomic takes, over the loop too
-        uint32_t c0, c1;
-        asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %3" : "=&v"(c0), "=v"(c1) : "v"(lo[k]), "v"(hi[k]) : "memory");
-        const int i = t + k * kThreads16;
-        if (c0) atomicAdd(&hist[2 * i], (unsigned long long)c0);
-        if (c1) atomicAdd(&hist[2 * i + 1], (unsigned long long)c1);
-    }
+    for (int k = 0; k < kWords; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t l = __shfl(lo[k], 32 * h + (lane >> 1), 64), u = __shfl(hi[k], 32 * h + (lane >> 1), 64);
+            const uint32_t c = odd ? u : l;
+            if (c) atomicAdd(&hist[base + 64 * h + 2 * k * kThreads16], (unsigned long long)c);
+        }
 }
 
 // ---- Otsu's threshold and 2 sigma of a histogram, on the device -------------
@@ -458,13 +479,19 @@ hipError_t launch_histogram(const void* vol, size_t n, int dtype, uint64_t* hist
         hipLaunchKernelGGL(hist_u8, dim3((unsigned)groups), dim3(kThreads), 0, s,
                            static_cast<const uint8_t*>(vol), n, chunk, h);
     } else {
-        // At most one workgroup per CU and per full chunk.  A chunk takes about
-        // 6.5 us, a further workgroup adds 0.08 us of flush (the occupied bins
-        // are the same, and their atomics meet): least at 9 sqrt(chunks), and up to
-        // 128 workgroups one chunk each.  A workgroup's counts stay below 2^32.
+        // At most one workgroup per CU.  A chunk takes about 6.5 us; what a
+        // further workgroup's flush adds depends on the occupied levels, 0.03 us
+        // for 4096 of them, 0.5 us for all: 9 sqrt(chunks), and up to 128
+        // workgroups one chunk each, lies between the two (2^23 voxels in 48, 128
+        // and 192 workgroups: 25, 18 and 13 us, and 46, 81 and 89).  Short volumes
+        // are spread over more than they have chunks for, as far as their few
+        // voxels bound the flush (2^15 voxels of all levels in 1 and 64
+        // workgroups: 14 and 10 us; 2^18 in 4 and 16: 21 and 14, of 4096 levels 17
+        // and 7).  A workgroup's counts stay below 2^32.
         const size_t nv = n / 8, full = nv / kVecs16 + 1;
         const size_t best = std::max<size_t>(128, (size_t)(9.0 * std::sqrt((double)full)));
-        const size_t groups = std::max(std::min({(size_t)device_cus(), full, best}), nv >> 28);
+        const size_t spread = std::min<size_t>(n <= 131072 ? 64 : 16, nv / 32 + 1);
+        const size_t groups = std::max(std::min({(size_t)device_cus(), std::max(full, spread), best}), nv >> 28);
         const size_t chunks = std::max<size_t>(1, (nv + groups * kVecs16 - 1) / (groups * kVecs16));
         const int cv = (int)((nv + groups * chunks - 1) / (groups * chunks));
         hipLaunchKernelGGL(hist_u16, dim3((unsigned)groups), dim3(kThreads16), 0, s,
