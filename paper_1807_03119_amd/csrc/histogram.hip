@@ -303,11 +303,12 @@ __global__ __launch_bounds__(kSelThreads) void select_scalar(
             uint64_t Q = 0;
             for (int w = 0; w < kSelWaves; ++w) Q += wq[w];
             const u128 num = 4 * ((u128)N * Q - (u128)S * S), n2 = (u128)N * N;
-            uint32_t w = 0;
-            for (int b = 17; b >= 0; --b) {
-                const uint64_t x = w | (1u << b);
-                if (n2 * (x * x) <= num) w = (uint32_t)x;  // below 2^100
-            }
+            // the fp64 root is off by less than 2^-32: at most one step (products
+            // below 2^100).  Eighteen 128-bit comparisons of one thread took 4 us.
+            const auto real = [](u128 v) { return (double)(uint64_t)(v >> 64) * 18446744073709551616.0 + (double)(uint64_t)v; };
+            uint32_t w = (uint32_t)__builtin_sqrt(real(num) / real(n2));
+            if (n2 * ((uint64_t)w * w) > num) --w;
+            if (n2 * ((uint64_t)(w + 1) * (w + 1)) <= num) ++w;
             *dev = w;
             *host = w;
         }
