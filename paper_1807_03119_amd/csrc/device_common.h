@@ -75,40 +75,6 @@ __device__ __forceinline__ void buffer_store(uint32_t v, rsrc_t r, uint32_t voff
         __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, voff, soff, POLICY);
 }
 
-// Direct buffer -> LDS load of one element per lane (LDS DMA).  The element is
-// zero-extended to 32 bits and written to LDS at dst + 4 * lane, where dst is
-// wave-uniform; the load bypasses VGPRs and completes asynchronously (vmcnt).
-template <typename T>
-__device__ __forceinline__ void buffer_load_lds(rsrc_t r, void* dst_wave, uint32_t voff);
-template <>
-__device__ __forceinline__ void buffer_load_lds<uint8_t>(rsrc_t r, void* dst_wave, uint32_t voff)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)dst_wave, 1, voff, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ void buffer_load_lds<uint16_t>(rsrc_t r, void* dst_wave, uint32_t voff)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)dst_wave, 2, voff, 0, 0, 0);
-}
-
-// LDS DMA of two adjacent elements per lane (the byte offset must be a multiple
-// of 2 * sizeof(T)): a uint16 pair fills the 32-bit LDS word, a uint8 pair
-// lands zero-extended in its low 16 bits.
-template <typename T>
-__device__ __forceinline__ void buffer_load_lds_pair(rsrc_t r, void* dst_wave, uint32_t voff);
-template <>
-__device__ __forceinline__ void buffer_load_lds_pair<uint8_t>(rsrc_t r, void* dst_wave,
-                                                              uint32_t voff)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)dst_wave, 2, voff, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ void buffer_load_lds_pair<uint16_t>(rsrc_t r, void* dst_wave,
-                                                               uint32_t voff)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)dst_wave, 4, voff, 0, 0, 0);
-}
-
 // Wait for this wave's outstanding vector-memory operations (including LDS DMA).
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

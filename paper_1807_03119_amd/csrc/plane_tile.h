@@ -271,7 +271,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
     const size_t plane = (size_t)g.nx * g.ny;
     const uint32_t pbytes = (uint32_t)(plane * sizeof(T));
 
-    // NQ tiles from r = 2 run as a two-barrier pipeline (below)
+    // uint8 and NQ tiles from r = 2 run as a two-barrier pipeline (below)
     constexpr bool PIPE = SM::PIPE;
     // ---- raw columns owned for the z-sums.  Pipelined tiles rotate them so
     // that the partial last round falls on the highest threads, whose waves
@@ -505,7 +505,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
     // unrolled block); the planes past the end read clamped slices and store
     // nothing
     const int npl = (z1 - z0) + 2 * D;
-    // NQ tiles from r = 2 run as a pipeline with two barriers per plane: the
+    // PIPE tiles (from r = 2: uint8, narrow squares) run with two barriers per plane: the
     // y-pass of the previous plane shares a phase with the z-sums of this one,
     // and its gather (issued first) a phase with this plane's x-pass; the keys
     // planes alternate (512^3, 12-bit: r = 3 467 -> 445 us per launch, 288 ->
@@ -513,6 +513,7 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
     // turn, three barriers a plane, in the loop below the pipelined one (kept
     // apart: folding the two into shared helpers cost r = 1 13 %).
     if constexpr (PIPE) {
+        static_assert(ORD && PAIR && !WIDE && !CROSS, "the pipeline's tiles: ordered keys, paired sums");
         constexpr int KSZ = SM::a16(S::GY * VP, 8);  // keys per plane
         auto kbuf = [&](int q) { return keys + ((q & 1) ? KSZ : 0); };
         // the packed key of one centre, written to plane kb
@@ -531,26 +532,16 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                 YQ cq[S::YW];
 #pragma unroll
                 for (int t = 0; t < S::YW; ++t) {
-                    if constexpr (PAIR) {
-                        const uint2 bq = *reinterpret_cast<const uint2*>(sm.xq + 2 * ((rbase + t) * S::XPD + ycol));
-                        cb[t] = t ? cb[t - 1] + bq.x : bq.x;
-                        cq[t] = t ? cq[t - 1] + (YQ)bq.y : (YQ)bq.y;
-                        continue;
-                    }
-                    const uint32_t b = sm.xb[(rbase + t) * S::XPB + ycol];
-                    cb[t] = t ? cb[t - 1] + b : b;
-                    if constexpr (VAR) {
-                        const YQ qv = (YQ)sm.xq[(rbase + t) * SM::XPQ + ycol];
-                        cq[t] = t ? cq[t - 1] + qv : qv;
-                    }
+                    const uint2 bq = *reinterpret_cast<const uint2*>(sm.xq + 2 * ((rbase + t) * S::XPD + ycol));
+                    cb[t] = t ? cb[t - 1] + bq.x : bq.x;
+                    cq[t] = t ? cq[t - 1] + (YQ)bq.y : (YQ)bq.y;
                 }
 #pragma unroll
                 for (int m = 0; m < YS; ++m) {
                     const int gy = rbase + m;
                     if (m + (S::NYS - 1) * YS < S::GY || gy < S::GY) {
                         const uint32_t b = cb[m + 2 * R] - (m ? cb[m - 1] : 0u);
-                        YQ qv = 0;
-                        if constexpr (VAR) qv = cq[m + 2 * R] - (m ? cq[m - 1] : (YQ)0);
+                        const YQ qv = cq[m + 2 * R] - (m ? cq[m - 1] : (YQ)0);
                         centre_key(kb, gy, ycol, b, qv);
                     }
                 }
@@ -567,66 +558,17 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
             for (int j = 0; j < OPT; ++j) {
                 const int oy = oyb + j * S::OROWS;
                 const int ic = (oy + D) * VP + ox + D;
-                uint32_t o;
-                if constexpr (ORD) {
-                    // cluster 0 is the centre, 1..4 the plane below, 5..8 above
-                    const uint64_t ck = kb[ic];
-                    uint64_t gk = kb[oy * VP + ox] | (1ull << 14);
+                // cluster 0 is the centre, 1..4 the plane below, 5..8 above
+                const uint64_t ck = kb[ic];
+                uint64_t gk = kb[oy * VP + ox] | (1ull << 14);
 #pragma unroll
-                    for (int k = 1; k < 4; ++k) {
-                        const int ik = (oy + ((k & 2) ? 2 * D : 0)) * VP + ox + ((k & 1) ? 2 * D : 0);
-                        gk = min_key(gk, kb[ik] | ((uint64_t)(k + 1) << 14));
-                    }
-                    o = (uint32_t)min_key(mk[ur][j], gk + kUpper) & 0x3fffu;
-                    mk[u][j] = min_key(ck, ak[ur][j]);
-                    ak[u][j] = gk;
-                } else if constexpr (PACK) {
-                    // c.v < b.v  <=>  c.key < (b.key & kHigh): the same
-                    // first minima as the unpacked branch below
-                    const uint64_t ck = kb[ic];
-                    uint64_t gk = kb[oy * VP + ox];
-#pragma unroll
-                    for (int k = 1; k < 4; ++k) {
-                        const int ik = (oy + ((k & 2) ? 2 * D : 0)) * VP + ox + ((k & 1) ? 2 * D : 0);
-                        const uint64_t kk = kb[ik];
-                        gk = kk < (gk & kHigh) ? kk : gk;
-                    }
-                    o = (uint32_t)(gk < (mk[ur][j] & kHigh) ? gk : mk[ur][j]) & 0xffffu;
-                    mk[u][j] = ak[ur][j] < (ck & kHigh) ? ak[ur][j] : ck;
-                    ak[u][j] = gk;
-                } else if constexpr (VAR) {
-                    const double cv = sm.vv[ic];
-                    const uint32_t co = sm.vo[ic];
-                    double gv = sm.vv[oy * VP + ox];
-                    uint32_t go = sm.vo[oy * VP + ox];
-#pragma unroll
-                    for (int k = 1; k < 4; ++k) {
-                        const int ik = (oy + ((k & 2) ? 2 * D : 0)) * VP + ox + ((k & 1) ? 2 * D : 0);
-                        const double v = sm.vv[ik];
-                        if (v < gv) {
-                            gv = v;
-                            go = sm.vo[ik];
-                        }
-                    }
-                    // output p - D: firstmin(C, G(p - 2D)) kept D planes, then G(p)
-                    o = gv < mv[ur][j] ? go : mo[ur][j];
-                    // output p: firstmin(C(p), G(p - D))
-                    const bool ta = av[ur][j] < cv;
-                    mv[u][j] = ta ? av[ur][j] : cv;
-                    mo[u][j] = ta ? ao[ur][j] : co;
-                    av[u][j] = gv;
-                    ao[u][j] = go;
-                } else {
-                    const uint32_t c = sm.vo[ic];
-                    const uint32_t k = sm.vo[oy * VP + ox] + sm.vo[oy * VP + ox + 2 * D] +
-                                       sm.vo[(oy + 2 * D) * VP + ox] +
-                                       sm.vo[(oy + 2 * D) * VP + ox + 2 * D];
-                    // output p - D: C + K(p - 2D) kept D planes, plus K(p)
-                    o = round_div_odd(mo[ur][j] + k, inv);
-                    // output p: C(p) + K(p - D)
-                    mo[u][j] = c + ao[ur][j];
-                    ao[u][j] = k;
+                for (int k = 1; k < 4; ++k) {
+                    const int ik = (oy + ((k & 2) ? 2 * D : 0)) * VP + ox + ((k & 1) ? 2 * D : 0);
+                    gk = min_key(gk, kb[ik] | ((uint64_t)(k + 1) << 14));
                 }
+                uint32_t o = (uint32_t)min_key(mk[ur][j], gk + kUpper) & 0x3fffu;
+                mk[u][j] = min_key(ck, ak[ur][j]);
+                ak[u][j] = gk;
                 if (GATE && o < gate) o = 0;
                 buffer_store<T>(o, wr, soff[j], 0u);
             }
@@ -642,37 +584,18 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                 for (int i = 0; i < S::NZ; ++i) {
                     const int d = (int)en[i] - (int)eo[i];
                     zb[i] += (uint32_t)d;
-                    if constexpr (VAR) {
-                        const uint32_t s = en[i] + eo[i];
-                        if constexpr (WIDE) zq[i] = __builtin_fma((double)d, (double)s, zq[i]);
-                        else if constexpr (NQ) zq[i] += (uint32_t)d * s;  // modulo 2^32
-                        else zq[i] += (uint32_t)(d * (int)s);
-                    }
+                    const uint32_t s = en[i] + eo[i];
+                    if constexpr (NQ) zq[i] += (uint32_t)d * s;  // modulo 2^32
+                    else zq[i] += (uint32_t)(d * (int)s);
                     if constexpr (NQ) orv |= en[i];
                 }
 #pragma unroll
                 for (int i = 0; i < S::NZ; ++i) {
-                    if (i < S::NZ - 1 || zlast) {
-                        if constexpr (PAIR) {
-                            *reinterpret_cast<uint2*>(sm.zb + zi[i]) = make_uint2(zb[i], (uint32_t)zq[i]);
-                            continue;
-                        }
-                        sm.zb[zi[i]] = zb[i];
-                        if constexpr (VAR) {
-                            if constexpr (WIDE) {
-                                const uint64_t w = __builtin_bit_cast(uint64_t, zq[i]);
-                                sm.zq0[zi[i]] = (uint32_t)w;
-                                sm.zq1[zi[i]] = (uint32_t)(w >> 32);
-                            } else {
-                                sm.zq0[zi[i]] = zq[i];
-                            }
-                        }
-                        if constexpr (CROSS) sm.ec[zi[i]] = ec[i];
-                    }
+                    if (i < S::NZ - 1 || zlast)
+                        *reinterpret_cast<uint2*>(sm.zb + zi[i]) = make_uint2(zb[i], (uint32_t)zq[i]);
                 }
                 load(en, p + 1 + R);
                 load(eo, p - R);
-                if constexpr (CROSS) load(ec, p + 1);
                 // NQ: at each block after the first, the values summed so far are
                 // checked (later planes of the block are checked at the next one,
                 // or after the loop)
@@ -683,35 +606,8 @@ __device__ __forceinline__ bool plane_tile(PTSmem<R, D, SHAPE, RULE, T, WT, NQ>&
                     if (u == 0 && qb > 0 && *flag) return false;
                 if (q > 0) gather(kbuf(q - 1), (u + U - 1) % U, q - 1);
 
-                // 2. cubes: x-pass of the z-sums.  Crosses: x-lines and y-lines
-                //    of slice p through every centre.
-                if constexpr (!CROSS) {
-                    xpass(sm.zb, sm.zq0, sm.zq1);
-                } else {
-                    xpass(sm.ec, nullptr, nullptr);
-                    if (yact) {
-                        // y-line of centre (ycol, c) covers raw rows c .. c+2r of
-                        // raw column ycol + r
-                        const int rbase = yseg * YS;
-                        uint32_t cb[S::YW];
-                        QT cq[S::YW];
-#pragma unroll
-                        for (int t = 0; t < S::YW; ++t) {
-                            const uint32_t e = sm.ec[(rbase + t) * S::ZP + ycol + R];
-                            cb[t] = t ? cb[t - 1] + e : e;
-                            if constexpr (VAR) cq[t] = t ? cq[t - 1] + sq(e) : sq(e);
-                        }
-#pragma unroll
-                        for (int m = 0; m < YS; ++m) {
-                            const int gy = rbase + m;
-                            if (m + (S::NYS - 1) * YS < S::GY || gy < S::GY) {
-                                sm.yb[gy * S::XPB + ycol] = cb[m + 2 * R] - (m ? cb[m - 1] : 0u);
-                                if constexpr (VAR)
-                                    sm.yq[gy * SM::XPQ + ycol] = cq[m + 2 * R] - (m ? cq[m - 1] : (QT)0);
-                            }
-                        }
-                    }
-                }
+                // 2. x-pass of the z-sums
+                xpass(sm.zb, sm.zq0, sm.zq1);
                 barrier_lds();
             }
         }
