@@ -26,7 +26,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak, GB/s
 # VALU peak in 32-bit lane operations per second: 256 CUs x 4 SIMDs x 16 lanes
-# x 2.4 GHz (the MINVAR9 kernel is bound by its VALU work, not by HBM)
+# x 2.4 GHz (the MINVAR9 kernel is bound by LDS throughput, then by this, not by HBM)
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 DIMS = (512, 512, 512)
 SEED = 2000

@@ -271,9 +271,12 @@ LNF_API int lnf_otsu_threshold(const uint64_t* hist, int levels, uint32_t* T);
 
 /*
  * The paper's automatic pipeline: T = Otsu threshold of `vol`, then the
- * context's rule gated at T (the context's own gate_T is not used).  Reads
- * the histogram back, so `stream` is synchronised once; *T (if not NULL)
- * receives the threshold.  Errors: as lnf_filter, LNF_ENOMEM.
+ * context's rule gated at T (the context's own gate_T is not used).  The
+ * threshold is found on the device.  The call waits until it is known: on
+ * return everything enqueued on `stream` before the call, and the histogram,
+ * have completed, while the filter may still be running; *T (if not NULL)
+ * holds the threshold.  Not while `stream` is captured (LNF_EHIP; nothing is
+ * enqueued).  Errors: as lnf_filter, LNF_ENOMEM.
  */
 LNF_API int lnf_filter_otsu(lnf_handle h, const void* vol, const int64_t dims[3], int dtype,
                             int radius, void* out, hipStream_t stream, uint32_t* T);
@@ -301,10 +304,12 @@ LNF_API int lnf_filter_otsu(lnf_handle h, const void* vol, const int64_t dims[3]
  *                    in the whole volume; weights and threshold in 2^-32 fixed
  *                    point (floor(x * 2^32 + 1/2), x in fp64 with the C
  *                    library's log2).
- * lnf_filter_mean and lnf_filter_okada are asynchronous on `stream`;
- * lnf_filter_sigma with half_width < 0 and lnf_filter_entropy read a
- * histogram back first (they synchronise `stream`).  Radius 1..LNF_RADIUS_MAX
- * (Okada: the six face neighbours only).
+ * lnf_filter_mean and lnf_filter_okada are asynchronous on `stream`, and so is
+ * lnf_filter_sigma with half_width >= 0.  With half_width < 0 it waits for w as
+ * lnf_filter_otsu does for T: the filter may still be running on return.
+ * lnf_filter_entropy reads a histogram back first (it synchronises `stream`),
+ * then enqueues the filter.  Neither of the two while `stream` is captured
+ * (LNF_EHIP).  Radius 1..LNF_RADIUS_MAX (Okada: the six face neighbours only).
  * Errors: as lnf_filter; LNF_EINVAL also for a non-finite t_e; LNF_ENOMEM.
  */
 LNF_API int lnf_filter_mean(lnf_handle h, const void* vol, const int64_t dims[3], int dtype,

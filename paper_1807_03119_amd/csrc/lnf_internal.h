@@ -39,7 +39,7 @@ hipError_t launch_mean9(const void* in, void* out, int dtype, int r, Geom g, uin
                         TileCfg cfg, hipStream_t s, TileCfg* plan = nullptr,
                         const uint32_t* gate_dev = nullptr);
 // Whether rows are staged and stored as whole 32-bit words (WORDS in
-// mean9_tile.h): every row of both volumes starts at one. 
+// mean9_tile.h): every row of both volumes starts at one.
 inline bool mean9_words_ok(const void* in, const void* out, int nx, int dtype)
 {
     return nx % (dtype == LNF_U8 ? 4 : 2) == 0 &&

@@ -313,37 +313,50 @@ constexpr float kTraffic[kNumVariants] = {2.4f, 1.6f, 4.f, 1.6f}, kInBatch[kNumV
 
 TileCfg mean9_class_tile(int variant, int dtype, int r, const std::vector<Geom>& g)
 {
-    constexpr int kDepths[] = {16, 24, 32, 48, 64, 96, 128, 192};
+    constexpr int kDepths[] = {16, 24, 32, 48, 64, 96, 128, 192}, kN = 8;
+    // strips and iterations of a strip by volume and depth, the same for every
+    // variant; the longest strip by depth, for rows that are whole words or not
+    std::vector<float> strips(g.size() * kN), iters(g.size() * kN);
+    float most[2][kN] = {};
+    double voxels = 0;
+    for (size_t q = 0; q < g.size(); ++q) {
+        voxels += (double)g[q].nx * g[q].ny * g[q].nz;
+        for (int i = 0; i < kN; ++i) {
+            const int nzs = (g[q].nz + kDepths[i] - 1) / kDepths[i];
+            strips[q * kN + i] = (float)nzs;
+            iters[q * kN + i] = (float)(tile_iterations((g[q].nz + nzs - 1) / nzs, r) + 3);
+            float& m = most[row_words(dtype, g[q].nx)][i];
+            m = std::max(m, iters[q * kN + i]);
+        }
+    }
     TileCfg best{0, 16};
     float best_cost = -1.f;
     const float cus = (float)device_cus();
-    double voxels = 0;
-    for (const Geom& q : g) voxels += (double)q.nx * q.ny * q.nz;
     const double passes = voxels * (dtype == LNF_U8 ? 1 : 2) / 4600.0 * (voxels < 134217728.0 ? 0.5 : 1.0);
     for (int v = 0; v < kNumVariants; ++v) {
         if (!tile_eligible(v, variant, dtype, r)) continue;
-        const float memory = (float)passes * kTraffic[v];
-        for (int depth : kDepths) {
-            float groups = 0.f;
-            for (const Geom& q : g) groups += (float)tile_groups(v, depth, q);
-            float work = 0.f, longest = 0.f, alone = 0.f;
-            bool rounds = false;
-            for (const Geom& q : g) {
-                const TileCost& c = cost_of(dtype, v, r, q);
-                const int resident = resident_of(c);
-                const int n = (int)std::min((groups + cus - 1.f) / cus, (float)resident);
-                const int nzs = (q.nz + depth - 1) / depth;
-                const float iters = (float)(tile_iterations((q.nz + nzs - 1) / nzs, r) + 3);
-                rounds = groups > cus * resident;
-                work += (float)tile_groups(v, depth, q) * iters * c.at[resident - 1] / resident;
-                longest = std::max(longest, iters * c.at[n - 1]);
-                alone = std::max(alone, iters * c.at[0]);
+        const TileCost* const c = (dtype == LNF_U8 ? kCostU8 : kCostU16)[r - 1][0] + v;
+        const TileCost* const cw = (dtype == LNF_U8 ? kCostU8 : kCostU16)[r - 1][1] + v;
+        const int resident = resident_of(*c);
+        float groups[kN] = {}, work[kN] = {};
+        for (size_t q = 0; q < g.size(); ++q) {
+            const float cols = (float)tile_groups(v, g[q].nz, g[q]);
+            const float tau = cols * (float)(row_words(dtype, g[q].nx) ? cw : c)->at[resident - 1] / (float)resident;
+            for (int i = 0; i < kN; ++i) {
+                groups[i] += cols * strips[q * kN + i];
+                work[i] += tau * strips[q * kN + i] * iters[q * kN + i];
             }
-            float cost = rounds ? std::max(work / cus + 0.75f * alone, longest) : longest;
-            cost = std::hypot(cost * kInBatch[v], memory);
+        }
+        for (int i = 0; i < kN; ++i) {
+            const int n = std::max(1, (int)std::min((groups[i] + cus - 1.f) / cus, (float)resident));
+            const float longest = std::max(most[0][i] * (float)c->at[n - 1], most[1][i] * (float)cw->at[n - 1]);
+            const float alone = std::max(most[0][i] * (float)c->at[0], most[1][i] * (float)cw->at[0]);
+            const bool rounds = groups[i] > cus * (float)resident;
+            const float time = rounds ? std::max(work[i] / cus + 0.75f * alone, longest) : longest;
+            const float cost = std::hypot(time * kInBatch[v], (float)passes * kTraffic[v]);
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
-                best = TileCfg{v, depth};
+                best = TileCfg{v, kDepths[i]};
             }
         }
     }

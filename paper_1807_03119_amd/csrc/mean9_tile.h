@@ -82,7 +82,8 @@ struct M9Geo {
 };
 
 // Waves per SIMD the tile kernels are compiled for: as many as the registers
-// allow without spills.
+// allow without spills (none but the 128 x 32 tile of uint16 at r = 4, with 120:
+// not a default, see mean9.hip).
 template <int R, int TY, typename T>
 constexpr int m9_waves()
 {
