@@ -528,6 +528,8 @@ def main():
         "value": gvox, "unit": "Gvoxel/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "warmup_launches": warm_n, "ms_per_step": ms,
         "higher_is_better": True, "scaling": "weak",
+        # exact integers; MEAN9's x- and y-passes are f16 products of byte digits
+        # summed in fp32 below 2^24, MINVAR9's variances fp64 below 2^53
         "vs_baseline": None, "dtype": "u32", "data": "synthetic",
         "config": {"workload": f"single {DIMS[0]}x{DIMS[1]}x{DIMS[2]} uint16 (12-bit) CT "
                                f"phantom, radius {args.radius}, {args.rule.upper()}",

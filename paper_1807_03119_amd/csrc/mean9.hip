@@ -43,30 +43,27 @@ __attribute__((amdgpu_waves_per_eu((m9_waves<R, TY, T>())))) void mean9_stream(
                                          min(z0 + zs, g.nz), gate, inv_div, (int)threadIdx.x);
 }
 
-// Strip depth of the mean filter: least (1 + workgroups of a CU) x (iterations of a
-// strip + 4), from strips at least 4 slices deep that give each CU up to 16.  An
-// iteration with n workgroups on a CU takes about 1 + n times as long as each of
-// them adds; iterations come in whole blocks of 2r+2 and include the 2r slices of
-// halo, the two of the pipeline.  On ten volumes of 101 x 133 x 75 to 512 x 512 x
-// 128, both types, r = 1..3, within 0.7 % of the best of twenty depths on average;
+// Strip depth of the mean filter, of those that fill whole blocks of 2r+2
+// iterations (a strip takes its slices, the 2r of halo and the two of the
+// pipeline): least (iterations + 4) x the time of the rounds that the CUs take,
+// 1 + n for n workgroups on a CU.  On ten volumes of 101 x 133 x 75 to 512 x 512 x 128,
+// both types, r = 1..3, within 0.7 % of the best of twenty depths on average;
 // strips of 16 slices at least, at the general cost, 11 % (203 x 301 x 99 uint16 r
 // = 1, odd rows: 17.3 -> 14.4 us; 101 x 133 x 75 r = 2: 12.9 -> 8.1).
-int box_depth(int tiles, int nz, int r)
+int box_depth(int tiles, int nz, int r, int resident)
 {
-    const int cus = device_cus(), most = std::max(1, nz / 4), d = 2 * r + 2;
+    const int cus = device_cus(), d = 2 * r + 2;
     int best = nz;
     long long best_cost = -1;
-    for (int per_cu = 1; per_cu <= 16; ++per_cu) {
-        int nzs = std::min(most, std::max(1, cus * per_cu / tiles));
-        const int zs = (nz + nzs - 1) / nzs;
-        nzs = (nz + zs - 1) / zs;
-        const long long n = ((long long)tiles * nzs + cus - 1) / cus;
-        const long long cost = (1 + n) * ((zs + 2 * r + 2 + d - 1) / d * d + 4);
+    for (long long k = ((long long)nz + 2 * d - 1) / d; k >= 2; k -= 1 + k / 64) {  // every one up to 64 blocks
+        const int zs = (int)std::min<long long>(nz, (k - 1) * d);
+        const long long n = ((long long)tiles * (((long long)nz + zs - 1) / zs) + cus - 1) / cus;
+        const long long full = n / resident, rest = n % resident;
+        const long long cost = (full * (1 + resident) + (rest ? 1 + rest : 0)) * (k * d + 4);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = zs;
         }
-        if (nzs >= most) break;
     }
     return best;
 }
@@ -77,7 +74,7 @@ hipError_t launch_box(const T* in, T* out, Geom g, uint32_t gate, hipStream_t s)
     constexpr int threads = M9Geo<R, 16, 64, T>::THREADS;
     const auto kern = mean9_stream<R, 16, T, GATE, 64, true>;
     const int tiles_x = (g.nx + 63) / 64, tiles_y = (g.ny + 15) / 16;
-    const int zs = box_depth(tiles_x * tiles_y, g.nz, R);
+    const int zs = box_depth(tiles_x * tiles_y, g.nz, R, resident_groups((const void*)kern, threads) / device_cus());
     const int total = tiles_x * tiles_y * ((g.nz + zs - 1) / zs);
     const int n = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
     const int words = mean9_words_ok(in, out, g.nx, sizeof(T) == 1 ? LNF_U8 : LNF_U16) ? 1 : 0;

@@ -95,7 +95,7 @@ template <int R, int TY, int TXW, typename T>
 struct M9Smem {
     using G = M9Geo<R, TY, TXW, T>;
     u32x4_t raw[G::NRB][G::NLOAD * G::THREADS];
-    T outs[2][TY][TXW + 16];  // pitch: the rows of a store fall in different banks
+    T outs[2][TY][TXW + 16];  // pitch: of the sixteen rows written at once eight (uint8: all) fall in different banks
 };
 
 // WORDS: every row of both volumes starts at a 32-bit word (mean9_words_ok) and
