@@ -80,14 +80,15 @@ double planes_cost(Geom g, double round)
 // The tile with the least estimated time.  A full round of wide tiles (2 to 4 on a
 // CU) takes 0.92 to 1.06 of one of narrow tiles (4 to 7), for the same outputs
 // from r = 2, so what decides is how well either fills its rounds and the rows: of
-// 500 random volumes (sides 48..900) the choice is on average within 0.2 % of the
-// faster tile; wide from 256 x 256 on was 2 to 4 % off (uint8 r = 2, 391 x 585 x
-// 251: 171 and 210 us, 716 x 370 x 31 41 and 49; r = 3, 512^3: 362 and 353).
+// 740 random volumes the choice is on average within 0.2 % of the faster tile
+// (0.5 % of those above 9 * 10^7 voxels); wide from 256 x 256 on was 2 to 4 % off
+// (uint8 r = 2, 391 x 585 x 251: 171 and 210 us, 716 x 370 x 31 41 and 49; r = 3,
+// 512^3: 362 and 353).
 template <typename T>
 int faster_variant(int r, Geom g)
 {
     switch (r) {
-    case 1: return planes_cost<1, T, true>(g, 1.06) < planes_cost<1, T, false>(g, 1.0);
+    case 1: return planes_cost<1, T, true>(g, sizeof(T) == 1 ? 1.04 : 1.06) < planes_cost<1, T, false>(g, 1.0);
     case 2: return planes_cost<2, T, true>(g, 0.96) < planes_cost<2, T, false>(g, 1.0);
     case 3: return planes_cost<3, T, true>(g, 0.92) < planes_cost<3, T, false>(g, 1.0);
     default: return 0;  // one shape
